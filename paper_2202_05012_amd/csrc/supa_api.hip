@@ -152,7 +152,7 @@ struct supa_ctx {
     uint64_t scratch_gen = 0;            // advanced by every scratch reallocation
     char *fixed = nullptr;               // this device's fixed scratch array (device address)
     unsigned long long *d_wclk = nullptr;   // per wave of the last propagation launch: start, end
-    int64_t last_waves = 0;
+    int64_t last_waves = 0, last_launched = 0;   // the grid, and the waves of it that had showers to start
     // launch settings picked by supa_autotune, per batch size
     struct Tuned {
         int64_t n;
@@ -506,8 +506,9 @@ extern "C" supa_status supa_last_wave_times(supa_ctx *c, float *ms, int32_t capa
     int rate_khz = 0;
     HIP_TRY(c, hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, c->device));
     const double to_ms = rate_khz > 0 ? 1.0 / rate_khz : 0.0;
+    // waves that a small batch leaves without a shower are not launched: idle
     for (int64_t q = 0; q < std::min<int64_t>(w, capacity); ++q)
-        ms[q] = (float)((double)(t[2 * q + 1] - t[2 * q]) * to_ms);
+        ms[q] = q < c->last_launched ? (float)((double)(t[2 * q + 1] - t[2 * q]) * to_ms) : 0.0f;
     return SUPA_OK;
 }
 
@@ -599,7 +600,7 @@ static supa_status check_call(supa_ctx *c, const supa_batch *b, supa_output *out
 struct Plan {
     bool tree, hits_out, images, recs, post;
     int N, nsub, phases;
-    int64_t n, waves, img_words;
+    int64_t n, waves, img_words;     // waves: what the scratch is sized for
     supa::Params P;
     float e_unscale;
     int64_t *d_hstart, *d_part;
@@ -781,6 +782,16 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
     P.seed_lo = (uint32_t)seed;
     P.seed_hi = (uint32_t)(seed >> 32);
     P.n = (int32_t)n;
+    // Showers per wave at first: one while every wave can have its own (a
+    // batch of few showers then runs on as many waves as it has showers: the
+    // time of such a call is the number of steps of its longest wave), up to
+    // SLOTS in flight otherwise.  The fixed array's layout is made for SLOTS.
+    const int64_t n_sub = (n + L.nsub - 1) / L.nsub;
+    P.claim0 = fixed ? supa::SLOTS
+                     : (int)std::max<int64_t>(1, std::min<int64_t>(supa::SLOTS, (n_sub + L.waves - 1) / L.waves));
+    P.claim1 = supa::SLOTS;
+    P.waves = (int32_t)std::min<int64_t>(L.waves, (n_sub + P.claim0 - 1) / P.claim0);
+    P.h_static = (L.recs && !fixed && L.nsub == 1 && h_chunks >= (int64_t)P.waves * supa::SLOTS) ? P.waves * supa::SLOTS : 0;
     P.sid_base = b->shower_id_base;
     P.outputs = outs;
     P.keys = (outs & SUPA_OUT_KEYS) != 0;
@@ -826,6 +837,7 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
         K.wave_clk = c->d_wclk;
     }
     c->last_waves = L.waves;
+    c->last_launched = P.waves;
     return SUPA_OK;
 }
 
@@ -854,7 +866,7 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
             HIP_TRY(c, supa::launch_cost_order(b->e0 + o, (int)nj, P.e_scale, L.d_ohist, L.d_order + o,
                                                c->n_cu, s_main));
         if (timed) HIP_TRY(c, hipEventRecord(ev_prop[j][0], s_main));
-        HIP_TRY(c, supa::launch_propagate(Pj, c->g.kinematics == SUPA_KIN_LITERAL, c->g.n_regions >= 2, (int)L.waves, s_main));
+        HIP_TRY(c, supa::launch_propagate(Pj, c->g.kinematics == SUPA_KIN_LITERAL, c->g.n_regions >= 2, P.waves, s_main));
         // later launches finish the subtree items the previous one exported
         for (int ph = 1; ph <= P.last_phase; ++ph) {
             supa::Params Pp = Pj;
@@ -967,7 +979,7 @@ static int finish(supa_ctx *c, const Plan &L, supa_output *out, bool fixed = fal
         const int64_t nf = std::max<int64_t>(0, (int64_t)h[supa::CTR_NEED_F] - c->pool_cap);
         c->spill_cap = (int)std::min<int64_t>((int64_t)1 << 30,
                                               std::max<int64_t>(c->spill_cap, round_up_pow2(nf + 1)));
-        if (L.recs && (int64_t)h[supa::CTR_HCHUNK] > c->h_chunks)
+        if (L.recs && (int64_t)h[supa::CTR_HCHUNK] + L.P.h_static > c->h_chunks)
             c->h_chunks = std::max(2 * c->h_chunks, hit_chunks_for(total_hits, L.waves));
         if (L.tree && (int64_t)h[supa::CTR_NCHUNK] > c->n_chunks)
             c->n_chunks = std::max(2 * c->n_chunks, node_chunks_for(total_nodes, L.waves));
@@ -979,7 +991,7 @@ static int finish(supa_ctx *c, const Plan &L, supa_output *out, bool fixed = fal
         c->broken = true;
         return fail(c, SUPA_ERR_DEVICE, "internal particle accounting error in the propagation kernel");
     }
-    out->total_steps = (int64_t)h[supa::CTR_STEPS];
+    out->total_steps = (int64_t)supa::ctr_steps(h);
     out->total_hits = L.hits_out ? total_hits : 0;
     out->total_nodes = L.tree ? total_nodes : 0;
     if (L.hits_out && total_hits > out->hit_capacity)

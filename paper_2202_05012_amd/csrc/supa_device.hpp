@@ -123,6 +123,9 @@ struct Params {
     float e_scale;              // 2^s
     uint32_t seed_lo, seed_hi;
     int32_t n;                  // showers in the batch
+    int32_t waves;              // waves launched for the showers (phase 0)
+    int32_t claim0, claim1;     // showers per wave at first (wave w: w * claim0 ...), per later claim
+    int32_t h_static;           // hit-log chunks handed out by position (SLOTS per wave), or 0
     uint32_t sid_base;
     uint32_t outputs;
     bool keys;                  // write path ids of hits and nodes
@@ -205,9 +208,8 @@ struct PlaceParams {
 // sub-batches, so that the placement of one overlaps the propagation of the
 // next).
 enum {
-    CTR_STEPS = 0,       // particle-steps
     CTR_FLAGS = 1,       // FLAG_* bits
-    CTR_NEED_F = 2,      // largest particle pool seen
+    CTR_NEED_F = 2,      // largest particle pool that did not fit the LDS
     CTR_HCHUNK = 3,      // hit-log chunks claimed
     CTR_NCHUNK = 4,      // node-log chunks claimed
     CTR_BLOCK = 8        // words per block
@@ -226,7 +228,18 @@ constexpr int CTR_ST = CTR_BLOCK * (1 + MAX_SUB);
 constexpr int CTR_ST_SHARES = CTR_ST;
 __host__ __device__ constexpr int ctr_st_out(int phase) { return CTR_ST + 1 + phase; }
 __host__ __device__ constexpr int ctr_st_claim(int phase) { return CTR_ST + 1 + MAX_PHASES + phase; }
-constexpr int CTR_WORDS = CTR_ST + 1 + 2 * MAX_PHASES;
+// Particle-steps are added once per wave at its end: into STEP_COPIES words
+// on cache lines of their own, summed when the counters are read.  Device
+// atomics of many waves on one line run one after the other (7-10 ns each
+// measured), so thousands of waves ending together would queue for it.
+constexpr int STEP_COPIES = 32, STEP_STRIDE = 16;
+constexpr int CTR_STEPS = (CTR_ST + 1 + 2 * MAX_PHASES + STEP_STRIDE - 1) / STEP_STRIDE * STEP_STRIDE;
+constexpr int CTR_WORDS = CTR_STEPS + STEP_COPIES * STEP_STRIDE;
+inline unsigned long long ctr_steps(const unsigned long long *ctr) {
+    unsigned long long t = 0;
+    for (int q = 0; q < STEP_COPIES; ++q) t += ctr[CTR_STEPS + q * STEP_STRIDE];
+    return t;
+}
 
 enum { FLAG_OVERFLOW = 1, FLAG_RANGE = 2, FLAG_INTERNAL = 4, FLAG_SHARE = 8 };
 

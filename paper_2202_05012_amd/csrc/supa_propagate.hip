@@ -313,7 +313,9 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     S.sid = S.e0 = 0u;
     S.live = S.hits = S.nodes = S.passes = S.escaped = S.backward = 0;
     S.e_esc = 0u;
-    S.hc = S.hs_c = -1;
+    // each slot's first log chunk goes by its position (no claim)
+    S.hc = P.h_static > 0 && (!SUB || P.phase == 0) ? (int)wave * SLOTS + (int)(lane & (SLOTS - 1)) : -1;
+    S.hs_c = -1;
     S.hf = S.hs_f = 0;
     S.sh = -1;
 
@@ -350,7 +352,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         if (hlog_full) return -1;
         unsigned long long got = 0;
         if (lane == 0) got = atomicAdd(&P.ctr[CTR_HCHUNK], 1ull);
-        const uint32_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
+        const uint32_t g = (uint32_t)P.h_static + (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
         if (g >= (uint32_t)P.h_chunks) {
             hlog_full = true;
             overflow = true;
@@ -405,11 +407,16 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         }
     };
 
-    // work comes in batches of SLOTS items; lane q < SLOTS prepares the
-    // initial state of item base + q.  The next batch is claimed one batch
-    // ahead, so its atomic has long returned when it is needed.
-    unsigned long long next_base = 0;
-    if (lane == 0) next_base = atomicAdd(&P.sub[SUB_WORK], (unsigned long long)SLOTS);
+    // work comes in batches of up to SLOTS items; lane q prepares the initial
+    // state of item base + q.  A wave's first batch goes by its position
+    // (showers wave * claim0 ...), later ones come from the work counter,
+    // which starts behind the first ones; a batch is claimed one ahead, so
+    // its atomic has long returned when it is needed, and no wave asks when
+    // nothing was left after the first batches.  (Every wave asking twice
+    // made an empty launch of 4,096 waves take 100-150 us: the atomics on
+    // one counter run one after the other.)  In later launches of a call the
+    // same holds for the items, one at a time.
+    uint32_t next_base = (uint32_t)wave * (uint32_t)((SUB && P.phase > 0) ? 1 : P.claim0);
     int b_left = 0, b_at = 0;
     int w_i = 0, w_ok = 0, w_fwd = 0;
     uint32_t w_e = 0u;
@@ -470,7 +477,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
             kc = __builtin_amdgcn_readfirstlane(max(kc, 2));
             unsigned long long gb = 0;
             if (lane == 0) gb = atomicAdd(&P.ctr[CTR_HCHUNK], (unsigned long long)kc);
-            base = __builtin_amdgcn_readfirstlane((int)(uint32_t)gb);
+            base = P.h_static + __builtin_amdgcn_readfirstlane((int)(uint32_t)gb);
             if ((int64_t)(uint32_t)base + kc > (int64_t)P.h_chunks) {
                 hlog_full = true;
                 overflow = true;        // rerun with a larger log
@@ -509,13 +516,15 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
             if (SUB && ph > 0) {
                 // an item exported by the previous launch: pending particles
                 // of one shared shower, taken into slot s as one more party
-                unsigned long long got = 0;
-                if (lane == 0) got = atomicAdd(&P.ctr[ctr_st_claim(ph)], 1ull);
-                const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
-                if (it >= (uint32_t)__builtin_amdgcn_readfirstlane((int)sub_l[SL_ITEMS_IN])) {
+                const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_base);
+                const uint32_t n_it = (uint32_t)__builtin_amdgcn_readfirstlane((int)sub_l[SL_ITEMS_IN]);
+                if (it >= n_it) {
                     exhausted = true;
                     break;
                 }
+                next_base = 0xffffffffu;
+                if (gridDim.x < n_it && lane == 0)
+                    next_base = gridDim.x + (uint32_t)atomicAdd(&P.ctr[ctr_st_claim(ph)], 1ull);
                 const uint32_t *items = (const uint32_t *)(uintptr_t)(*(const uint64_t *)(sub_l + SL_ITEMS));
                 const int64_t cap = (int64_t)__builtin_amdgcn_readfirstlane((int)sub_l[SL_ITEM_CAP]);
                 const uint32_t *item = items + ((int64_t)((ph - 1) & 1) * cap + it) * ITEM_WORDS;
@@ -554,13 +563,17 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                 continue;
             }
             if (b_at == b_left) {
-                const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)next_base);
+                const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_base);
                 if (base >= (uint32_t)P.n) {
                     exhausted = true;
                     break;
                 }
-                if (lane == 0) next_base = atomicAdd(&P.sub[SUB_WORK], (unsigned long long)SLOTS);
-                b_left = min(SLOTS, P.n - (int)base);
+                const uint32_t first = (uint32_t)P.waves * (uint32_t)P.claim0;
+                next_base = 0xffffffffu;
+                if (first < (uint32_t)P.n && lane == 0)
+                    next_base = (uint32_t)min<unsigned long long>(
+                        first + atomicAdd(&P.sub[SUB_WORK], (unsigned long long)P.claim1), 0xffffffffull);
+                b_left = min(base < first ? P.claim0 : P.claim1, P.n - (int)base);
                 b_at = 0;
                 if ((int)lane < b_left) {
                     // initial condition (section "Using SUPA": energy, angle, impact point)
@@ -911,7 +924,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                 // the wave's claim of its next showers is already back.)
                 const int et = __builtin_amdgcn_readfirstlane((int)sub_l[SL_EXPORT]);
                 const bool no_new = __builtin_amdgcn_readfirstlane((int)sub_l[SL_PHASE]) > 0 ||
-                                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)next_base) >= (uint32_t)P.n;
+                                    (uint32_t)__builtin_amdgcn_readfirstlane((int)next_base) >= (uint32_t)P.n;
                 if (no_new && et >= 0 && top - bot >= et + WAVE) {
                     if (bot < lo) __threadfence_block();
                     const Entry e = pool_load(bot + (int)lane);
@@ -1053,8 +1066,8 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     // close the open node-log chunk
     if (lane == 0) {
         if (TREE && nc >= 0) P.nfill[nc] = (uint32_t)nf;
-        atomicAdd(&P.ctr[CTR_STEPS], steps);
-        atomicMax(&P.ctr[CTR_NEED_F], (unsigned long long)max_top);
+        if (steps) atomicAdd(&P.ctr[CTR_STEPS + STEP_STRIDE * ((int)wave & (STEP_COPIES - 1))], steps);
+        if (max_top > PC) atomicMax(&P.ctr[CTR_NEED_F], (unsigned long long)max_top);
     }
     if (wave_ballot(overflow) && lane == 0) atomicOr(&P.ctr[CTR_FLAGS], (unsigned long long)FLAG_OVERFLOW);
     if (lane == 0 && COLD(wave_clk) && (!SUB || P.phase == 0))
@@ -1062,7 +1075,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
 }
 
 __global__ void supa_zero_counters(unsigned long long *ctr) {
-    if (threadIdx.x < CTR_WORDS) ctr[threadIdx.x] = 0ull;
+    for (int q = threadIdx.x; q < CTR_WORDS; q += blockDim.x) ctr[q] = 0ull;
 }
 
 // the node-log chunks claimed so far, noted for a sub-batch
@@ -1091,8 +1104,7 @@ __global__ void supa_azimuth_kernel(const uint32_t *w, int64_t n, float *s, floa
 // host-side launchers (called by the C ABI in supa_api.hip)
 // ---------------------------------------------------------------------------
 hipError_t launch_zero_counters(unsigned long long *ctr, hipStream_t s) {
-    static_assert(CTR_WORDS <= 128, "one workgroup clears the counters");
-    hipLaunchKernelGGL(supa_zero_counters, dim3(1), dim3(128), 0, s, ctr);
+    hipLaunchKernelGGL(supa_zero_counters, dim3(1), dim3(256), 0, s, ctr);
     return hipGetLastError();
 }
 
