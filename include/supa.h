@@ -328,11 +328,14 @@ supa_status supa_set_schedule(supa_ctx *ctx, int32_t sub_batches, int32_t cost_o
  * empty (while showers remain to be started every wave is busy anyway).
  *   phases       0 (default): automatic -- 2 when the batch's showers all
  *                start at once on at most a quarter of the waves (4 n <= the
- *                waves launched), the kinematics are plain and no sub-batches
- *                are asked for, else 1; 1: no items; 2 .. 4: that many
- *                launches;
+ *                waves launched), the geometry has more than 8 planes, the
+ *                kinematics are plain and no sub-batches are asked for, else
+ *                1; 1: no items; 2 .. 4: that many launches;
  *   export_pool  pending particles beyond one step (64) from which a wave
- *                exports (default 0: every wave with 64 or more).
+ *                exports (default 0: every wave with 64 or more).  With
+ *                phases 0 and export_pool 0 a wave instead runs its shower
+ *                breadth first and, at 256 pending particles, deals all of
+ *                them out to items of 8 to 64.
  * Items need the plain kinematics without regional parameters (INVALID_ARG
  * for phases > 1 otherwise; automatic then means 1).  A call with items runs
  * as one sub-batch; supa_simulate_noalloc decides automatic as 1.  Items and shared

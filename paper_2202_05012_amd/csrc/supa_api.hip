@@ -67,6 +67,11 @@ static constexpr int kMaxImageWidth = 1024;
 // (context scratch; the fixed array holds fewer).  When they run out, waves
 // stop exporting and finish their showers themselves.
 static constexpr int kItemCap = 16384, kShareCap = 16384;
+// pending particles at which an expanding wave deals its shower out: every
+// tested size of shower was fastest or within 5% at 256 (128: 3 to 20%
+// slower for E0 = 1000; 384: E0 = 200 rarely reaches it, 40% slower), and
+// E0 <= 100 stays below it, where sharing costs more than it gives
+static constexpr int kExpand = 256;
 static constexpr int kFixedItemCap = 1024, kFixedShareCap = 1024;
 static constexpr int64_t kAutoOrderMin = 65536;     // automatic cost order: from this batch size
 
@@ -268,10 +273,16 @@ extern "C" supa_status supa_validate_geometry(const supa_geometry *g) {
 }
 
 // hit-log chunks that hold `records` records for `waves` waves: full chunks,
-// plus the partly filled chunk every shower slot may leave at the end
-static int64_t hit_chunks_for(int64_t records, int64_t waves) {
-    return (records + supa::HIT_CHUNK - 1) / supa::HIT_CHUNK + waves * supa::SLOTS + 8;
+// plus the partly filled chunk every shower slot may leave at the end and
+// what a wave has left of its last claim of `grab` chunks
+static int64_t hit_chunks_for(int64_t records, int64_t waves, int64_t grab = 1) {
+    return (records + supa::HIT_CHUNK - 1) / supa::HIT_CHUNK + waves * (supa::SLOTS + grab - 1) + 8;
 }
+
+// Log chunks per claim: four once the waves take several batches of showers
+// each (the claims of all waves meet on one counter; 100,000 showers:
+// propagation 1.290 -> 1.215 ms), else one at a time.
+static int64_t chunk_grab(int64_t n, int64_t waves) { return n > supa::SLOTS * waves ? 4 : 1; }
 
 // node-log chunks: a closed chunk may leave up to 127 records unused (a
 // phase appends at most 2 per lane), plus one open chunk per wave
@@ -637,13 +648,14 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
     int nsub = force_nsub > 0 ? force_nsub : (c->sub_batches > 0 ? c->sub_batches : 1);
     // subtree work items: automatic (0) = one export round when every shower
     // of the batch starts at once on at most a quarter of the waves (the
-    // rest would idle behind the largest showers) and nothing else asks for
-    // the single-launch path; measured to cost more than it saves once the
-    // showers fill the waves
+    // rest would idle behind the largest showers), the planes let a shower
+    // grow to kExpand pending particles (at most 2^(N-1)) and nothing else
+    // asks for the single-launch path; measured to cost more than it saves
+    // once the showers fill the waves
     const bool plain = c->g.kinematics != SUPA_KIN_LITERAL && c->g.n_regions < 2;
     int phases = c->phases;
     if (phases == 0)
-        phases = (plain && !fixed && nsub <= 1 && force_nsub <= 1 && (int64_t)supa::SLOTS * n <= L.waves) ? 2 : 1;
+        phases = (plain && !fixed && L.N > 8 && nsub <= 1 && force_nsub <= 1 && (int64_t)supa::SLOTS * n <= L.waves) ? 2 : 1;
     L.phases = plain ? phases : 1;
     if (!L.post || L.phases > 1) nsub = 1;
     L.nsub = (int)std::min<int64_t>(std::min(nsub, supa::MAX_SUB), n);
@@ -789,9 +801,14 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
     const int64_t n_sub = (n + L.nsub - 1) / L.nsub;
     P.claim0 = fixed ? supa::SLOTS
                      : (int)std::max<int64_t>(1, std::min<int64_t>(supa::SLOTS, (n_sub + L.waves - 1) / L.waves));
-    P.claim1 = supa::SLOTS;
+    // later claims: two at a time while a wave gets at most about 32 showers in
+    // all (a shorter tail: 20,000 showers 0.46 -> 0.40 ms, 100,000 1.215 ->
+    // 1.193 ms), SLOTS beyond (fewer claims: 250,000 showers of a wide energy
+    // range 6.59 ms against 6.68 ms)
+    P.claim1 = (!fixed && n_sub <= 32 * L.waves) ? 2 : supa::SLOTS;
     P.waves = (int32_t)std::min<int64_t>(L.waves, (n_sub + P.claim0 - 1) / P.claim0);
-    P.h_static = (L.recs && !fixed && L.nsub == 1 && h_chunks >= (int64_t)P.waves * supa::SLOTS) ? P.waves * supa::SLOTS : 0;
+    P.h_static = (L.recs && !fixed && L.nsub == 1 && h_chunks >= (int64_t)P.waves * P.claim0) ? P.waves * P.claim0 : 0;
+    P.h_grab = (L.recs && !fixed && L.nsub == 1) ? (int)chunk_grab(n, L.waves) : 1;
     P.sid_base = b->shower_id_base;
     P.outputs = outs;
     P.keys = (outs & SUPA_OUT_KEYS) != 0;
@@ -810,6 +827,14 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
     P.phase = 0;
     P.last_phase = subtrees ? L.phases - 1 : 0;
     P.export_top = c->export_top;
+    // Automatic items: the first launch runs each shower breadth first until
+    // it can be dealt out (kExpand pending particles, about six full steps),
+    // the second finishes the items.  Larger items for more showers: with
+    // 256 showers of E0 = 1000 and a tree 500 us per call at 32 particles
+    // (561 at 16, 615 at 8: half-empty steps), with 16 showers 291 us at 8
+    // (302 at 16, 327 at 32: too few waves).
+    P.expand = subtrees && c->phases == 0 && c->export_top == 0 ? kExpand : 0;
+    P.item_size = (int)std::max<int64_t>(8, std::min<int64_t>(supa::SUB_ITEM_MAX, n / 8));
     P.items = (uint32_t *)items_p;
     P.item_cap = item_cap;
     P.shares = (uint32_t *)shares_p;
@@ -866,11 +891,16 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
             HIP_TRY(c, supa::launch_cost_order(b->e0 + o, (int)nj, P.e_scale, L.d_ohist, L.d_order + o,
                                                c->n_cu, s_main));
         if (timed) HIP_TRY(c, hipEventRecord(ev_prop[j][0], s_main));
+        // up to kExpand pending particles and a step's daughters in LDS, where
+        // breadth first can take them in order
+        static_assert(kExpand + 128 <= 512, "no spill while a shower is expanded");
+        if (P.expand > 0) Pj.pool_cap = std::max(P.pool_cap, 512);
         HIP_TRY(c, supa::launch_propagate(Pj, c->g.kinematics == SUPA_KIN_LITERAL, c->g.n_regions >= 2, P.waves, s_main));
         // later launches finish the subtree items the previous one exported
         for (int ph = 1; ph <= P.last_phase; ++ph) {
             supa::Params Pp = Pj;
             Pp.phase = ph;
+            Pp.pool_cap = P.pool_cap;
             HIP_TRY(c, supa::launch_propagate(Pp, false, false, (int)L.waves, s_main));
         }
         if (L.tree) HIP_TRY(c, supa::launch_note_chunks(L.ctr, sub_ctr(j), s_main));
@@ -980,7 +1010,7 @@ static int finish(supa_ctx *c, const Plan &L, supa_output *out, bool fixed = fal
         c->spill_cap = (int)std::min<int64_t>((int64_t)1 << 30,
                                               std::max<int64_t>(c->spill_cap, round_up_pow2(nf + 1)));
         if (L.recs && (int64_t)h[supa::CTR_HCHUNK] + L.P.h_static > c->h_chunks)
-            c->h_chunks = std::max(2 * c->h_chunks, hit_chunks_for(total_hits, L.waves));
+            c->h_chunks = std::max(2 * c->h_chunks, hit_chunks_for(total_hits, L.waves, L.P.h_grab));
         if (L.tree && (int64_t)h[supa::CTR_NCHUNK] > c->n_chunks)
             c->n_chunks = std::max(2 * c->n_chunks, node_chunks_for(total_nodes, L.waves));
         return -1;
@@ -1008,7 +1038,7 @@ static void size_logs(supa_ctx *c, const supa_batch *b, const supa_output *out) 
     const int64_t waves = std::max(1, c->n_cu * c->waves_per_cu);
     if (outs & (SUPA_OUT_HITS | SUPA_OUT_IMAGES)) {
         const int64_t hint = (outs & SUPA_OUT_HITS) ? out->hit_capacity : 64 * b->n;
-        c->h_chunks = std::max(c->h_chunks, hit_chunks_for(std::min<int64_t>(hint, (int64_t)1 << 28), waves));
+        c->h_chunks = std::max(c->h_chunks, hit_chunks_for(std::min<int64_t>(hint, (int64_t)1 << 28), waves, chunk_grab(b->n, waves)));
     }
     if (outs & SUPA_OUT_TREE)
         c->n_chunks = std::max(c->n_chunks,

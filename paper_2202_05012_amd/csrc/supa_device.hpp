@@ -125,7 +125,8 @@ struct Params {
     int32_t n;                  // showers in the batch
     int32_t waves;              // waves launched for the showers (phase 0)
     int32_t claim0, claim1;     // showers per wave at first (wave w: w * claim0 ...), per later claim
-    int32_t h_static;           // hit-log chunks handed out by position (SLOTS per wave), or 0
+    int32_t h_static;           // hit-log chunks handed out by position (claim0 per wave), or 0
+    int32_t h_grab;             // hit-log chunks a wave claims at once after those
     uint32_t sid_base;
     uint32_t outputs;
     bool keys;                  // write path ids of hits and nodes
@@ -145,6 +146,8 @@ struct Params {
     // pending particles of a shower whose pool holds export_top + WAVE or
     // more entries; export_top < 0 disables it.
     int32_t phase, last_phase, export_top;
+    int32_t expand, item_size;  // launches before the last run breadth first up to `expand` pending
+                                // particles, then hand all of them out in items (0: export_top rule)
     uint32_t *items;            // two regions of item_cap items, ITEM_WORDS each
     int32_t item_cap;
     uint32_t *shares;           // share_cap records of SHARE_WORDS
@@ -252,14 +255,16 @@ enum { FLAG_OVERFLOW = 1, FLAG_RANGE = 2, FLAG_INTERNAL = 4, FLAG_SHARE = 8 };
 // through SH_KCAP chunks reserved and linked at conversion (SH_BASE ...), at
 // positions taken from SH_FILL.  With a tree, node indices come from SH_NODES.
 enum {
-    SH_I = 0, SH_SID, SH_E0, SH_HS_LO, SH_HS_HI, SH_FILL, SH_CONV_C, SH_CONV_F, SH_BASE, SH_KCAP,
-    SH_NODES, SH_HITS, SH_PASSES, SH_ESC, SH_BACK, SH_EESC, SH_ECUT, SH_ESTOP, SH_OUT, SH_FIELDS
+    SH_I = 0, SH_SID, SH_E0, SH_HS_LO, SH_HS_HI, SH_CONV_C, SH_CONV_F, SH_BASE, SH_KCAP, SH_PAD,
+    SH_FILL, SH_NODES, SH_HITS, SH_PASSES, SH_ESC, SH_BACK, SH_EESC, SH_ECUT, SH_ESTOP, SH_OUT, SH_FIELDS
 };
 constexpr int SHARE_WORDS = 32;
+static_assert(SH_FILL % 2 == 0 && SH_NODES == SH_FILL + 1, "one 64-bit counter of records and nodes");
 static_assert(SH_FIELDS <= SHARE_WORDS, "share record fits");
 // An item: up to 64 pending particles of one shared shower, as pool fields
 // [POOL_FIELDS][64] (KS = plane | share << 8), then the count.
 constexpr int ITEM_WORDS = 9 * 64 + 1;
+constexpr int SUB_ITEM_MAX = 64;
 constexpr int ITEM_MIN = 16;          // fewer particles of one shower are not exported
 
 // true when the propagation of this call failed (its outputs are rerun or

@@ -215,9 +215,15 @@ __device__ __forceinline__ int wave_excl_scan(int v) {
     return incl - v;
 }
 
+// Every vector memory operation of this wave so far has completed (device
+// atomics have been performed).  Orders a wave's accesses to a share record,
+// all of them agent-scope atomics, without a fence: __threadfence would write
+// back and invalidate whole caches at every party's end.
+__device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // parameters of subtree work items, kept in LDS (the scalar file is full)
 enum { SL_EXPORT = 0, SL_PHASE, SL_ITEMS_IN, SL_ITEM_CAP, SL_SHARE_CAP, SL_MARGIN, SL_ITEMS, SL_SHARES = SL_ITEMS + 2,
-       SUB_LDS_WORDS = 16 };
+       SL_EXPAND = SL_SHARES + 2, SL_ISIZE, SUB_LDS_WORDS = 16 };
 // LDS words of one wave: pool + the stop / split thresholds of every plane
 // pool, then the thresholds c1, c2 (u64) of 64 planes, of 4 rings with
 // regional parameters
@@ -265,7 +271,9 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     uint32_t *const sub_l = (uint32_t *)(thr + 2 * TN);
     if (SUB && lane == 0) {
         const int ph = P.phase;
-        sub_l[SL_EXPORT] = (uint32_t)((ph < P.last_phase && P.export_top >= 0) ? P.export_top : -1);
+        sub_l[SL_EXPORT] = (uint32_t)((ph < P.last_phase && P.export_top >= 0 && P.expand == 0) ? P.export_top : -1);
+        sub_l[SL_EXPAND] = (uint32_t)(ph < P.last_phase ? P.expand : 0);
+        sub_l[SL_ISIZE] = (uint32_t)P.item_size;
         sub_l[SL_PHASE] = (uint32_t)ph;
         const unsigned long long got =
             ph > 0 ? __hip_atomic_load(&P.ctr[ctr_st_out(ph - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
@@ -313,8 +321,8 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
     S.sid = S.e0 = 0u;
     S.live = S.hits = S.nodes = S.passes = S.escaped = S.backward = 0;
     S.e_esc = 0u;
-    // each slot's first log chunk goes by its position (no claim)
-    S.hc = P.h_static > 0 && (!SUB || P.phase == 0) ? (int)wave * SLOTS + (int)(lane & (SLOTS - 1)) : -1;
+    // the first log chunk of each slot in use at first goes by position (no claim)
+    S.hc = P.h_static > 0 && (int)lane < P.claim0 && (!SUB || P.phase == 0) ? (int)wave * P.claim0 + (int)lane : -1;
     S.hs_c = -1;
     S.hf = S.hs_f = 0;
     S.sh = -1;
@@ -347,12 +355,18 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         return true;
     };
     // a fresh hit-log chunk, or -1 once the log is full
+    // (P.h_grab at a time)
     bool hlog_full = false;
+    uint32_t hq = 0, hq_end = 0;
     auto claim_hit_chunk = [&]() -> int {
         if (hlog_full) return -1;
-        unsigned long long got = 0;
-        if (lane == 0) got = atomicAdd(&P.ctr[CTR_HCHUNK], 1ull);
-        const uint32_t g = (uint32_t)P.h_static + (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
+        if (hq == hq_end) {
+            unsigned long long got = 0;
+            if (lane == 0) got = atomicAdd(&P.ctr[CTR_HCHUNK], (unsigned long long)P.h_grab);
+            hq = (uint32_t)P.h_static + (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
+            hq_end = hq + (uint32_t)P.h_grab;
+        }
+        const uint32_t g = hq++;
         if (g >= (uint32_t)P.h_chunks) {
             hlog_full = true;
             overflow = true;
@@ -495,8 +509,11 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                          : f == SH_BASE ? (uint32_t)base : f == SH_KCAP ? (uint32_t)kc
                          : f == SH_NODES ? (TREE ? (uint32_t)slot_get(S.nodes, q) : 0u)
                          : f == SH_OUT ? 1u : 0u;
-        if (f < (uint32_t)SH_FIELDS) *share_ptr((int)sh, (int)f) = v;
-        __threadfence();
+        // stored past the caches (like every access to a share) and complete
+        // before any counter of the share is touched
+        if (f < (uint32_t)SH_FIELDS)
+            __hip_atomic_store(share_ptr((int)sh, (int)f), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wait_vmem();
         if ((int)lane == q) {
             S.sh = (int)sh;
             S.hs_c = base;
@@ -511,6 +528,10 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         while (top - bot < WAVE && !exhausted) {
             const uint64_t free_slots = wave_ballot((int)lane < SLOTS && S.i < 0);
             if (!free_slots) break;
+            // a wave that expands a shower breadth first holds no other
+            if (SUB && __builtin_amdgcn_readfirstlane((int)sub_l[SL_EXPAND]) > 0 &&
+                wave_ballot((int)lane < SLOTS && S.i >= 0))
+                break;
             const int s = __builtin_ctzll(free_slots);
             const int ph = SUB ? __builtin_amdgcn_readfirstlane((int)sub_l[SL_PHASE]) : 0;
             if (SUB && ph > 0) {
@@ -532,7 +553,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                 Entry e{0.f, 0.f, 0.f, 0.f, 0u, 0u, 0u, 0, 0u};
                 if ((int)lane < cnt) e = load_entry(item, WAVE, lane);
                 const int sh = __builtin_amdgcn_readfirstlane((int)(e.ks >> 8));
-                const uint32_t fv = (int)lane < SH_NODES ? share_load(sh, (int)lane) : 0u;
+                const uint32_t fv = (int)lane < SH_FILL ? share_load(sh, (int)lane) : 0u;
                 const int v_i = __builtin_amdgcn_readlane((int)fv, SH_I);
                 const uint32_t v_sid = (uint32_t)__builtin_amdgcn_readlane((int)fv, SH_SID);
                 const uint32_t v_e0 = (uint32_t)__builtin_amdgcn_readlane((int)fv, SH_E0);
@@ -682,14 +703,21 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
             // to plane k+1 at once, and deposits there if below threshold
             const int nb = min(WAVE, top - bot);
             const bool valid = (int)lane < nb;
-            const int j = top - 1 - (int)lane;
-            if (top - nb < lo) __threadfence_block();    // spilled entries: see other lanes' stores
+            // breadth first (the oldest entries; all of them are in LDS then) or depth first
+            const bool bfs = SUB && __builtin_amdgcn_readfirstlane((int)sub_l[SL_EXPAND]) > 0;
+            const int j = bfs ? bot + (int)lane : top - 1 - (int)lane;
+            if (!bfs && top - nb < lo) __threadfence_block();    // spilled entries: see other lanes' stores
             // lanes past the pending particles load the top entry again: every
             // use of p below is masked by this step's flags, so its values
             // need no clearing first
             const Entry p = pool_load(valid ? j : top - 1);
-            top -= nb;
-            lo = min(lo, top);
+            if (bfs) {
+                bot += nb;
+                lo = max(lo, bot);
+            } else {
+                top -= nb;
+                lo = min(lo, top);
+            }
             const int k = (int)(p.ks & 255u), slot = (int)(p.ks >> 8);
             // the lanes of each shower slot; `mine`: this lane's slot, `own`:
             // in lanes 0..SLOTS-1, the lanes of slot `lane` (whose state the
@@ -765,11 +793,20 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
             const uint64_t mesc = wave_ballot(esc_n > 0);
             // node index of daughter a: the slot's node count + 2 per split
             // below (a shared shower's next indices come from its share)
-            if (SUB && TREE && msplit) {
+            // one 64-bit atomic per shared slot and step takes the run's next
+            // record positions and the next node indices together
+            int fb_own = 0;
+            if (SUB && (TREE || recs)) {
                 const bool shs = (int)lane < SLOTS && S.sh >= 0;
                 if (wave_ballot(shs)) {
-                    const int ns = (int)__popcll(msplit & own);
-                    if (shs && ns > 0) S.nodes = (int)atomicAdd(share_ptr(S.sh, SH_NODES), (uint32_t)(2 * ns));
+                    const uint32_t nr = (uint32_t)(__popcll(mh1 & own) + __popcll(mh2 & own));
+                    const uint32_t ns = TREE ? 2u * (uint32_t)__popcll(msplit & own) : 0u;
+                    if (shs && (nr | ns)) {
+                        const unsigned long long g =
+                            atomicAdd((unsigned long long *)share_ptr(S.sh, SH_FILL), ((unsigned long long)ns << 32) | nr);
+                        fb_own = (int)(uint32_t)g;
+                        if (TREE) S.nodes = (int)(uint32_t)(g >> 32);
+                    }
                 }
             }
             const int node_a = __shfl(S.nodes, slot, WAVE) + 2 * (int)lanes_below(msplit & mine);
@@ -800,9 +837,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                     // through the reserved chunks
                     const bool shs = (int)lane < SLOTS && S.sh >= 0;
                     if (wave_ballot(shs)) {
-                        int fb = 0;
-                        if (shs && cnt_own > 0) fb = (int)atomicAdd(share_ptr(S.sh, SH_FILL), (uint32_t)cnt_own);
-                        const int fbs = __shfl(fb, slot, WAVE);
+                        const int fbs = __shfl(fb_own, slot, WAVE);
                         const bool mysh = __shfl(S.sh, slot, WAVE) >= 0;
                         const int kb = __shfl(S.hs_c, slot, WAVE), kn = __shfl(S.hs_f, slot, WAVE);
                         if (mysh) {
@@ -925,7 +960,49 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                 const int et = __builtin_amdgcn_readfirstlane((int)sub_l[SL_EXPORT]);
                 const bool no_new = __builtin_amdgcn_readfirstlane((int)sub_l[SL_PHASE]) > 0 ||
                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)next_base) >= (uint32_t)P.n;
-                if (no_new && et >= 0 && top - bot >= et + WAVE) {
+                const int ex = __builtin_amdgcn_readfirstlane((int)sub_l[SL_EXPAND]);
+                if (no_new && ex > 0 && top - bot >= ex) {
+                    // ---- the expanded shower leaves whole: its pending
+                    // particles dealt out in turn (equal shares of old and
+                    // young ones) to items of about item_size
+                    const int q = __builtin_ctzll(active);
+                    int sh = slot_get(S.sh, q);
+                    if (sh < 0) sh = convert(q);
+                    int gone = 0;
+                    if (sh >= 0) {
+                        const int cnt = top - bot;
+                        const int isz = __builtin_amdgcn_readfirstlane((int)sub_l[SL_ISIZE]);
+                        const int ph = __builtin_amdgcn_readfirstlane((int)sub_l[SL_PHASE]);
+                        const int64_t cap = (int64_t)__builtin_amdgcn_readfirstlane((int)sub_l[SL_ITEM_CAP]);
+                        int ni = (cnt + isz - 1) / isz;
+                        unsigned long long got = 0;
+                        if (lane == 0) got = atomicAdd(&P.ctr[ctr_st_out(ph)], (unsigned long long)ni);
+                        const uint32_t it0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)got);
+                        ni = (int)min<int64_t>(ni, cap - (int64_t)it0);
+                        if (ni > 0) {
+                            gone = min(cnt, WAVE * ni);
+                            if (lane == 0) atomicAdd(share_ptr(sh, SH_OUT), (uint32_t)ni);
+                            wait_vmem();
+                            uint32_t *items = (uint32_t *)(uintptr_t)(*(const uint64_t *)(sub_l + SL_ITEMS));
+                            uint32_t *item0 = items + ((int64_t)(ph & 1) * cap + it0) * ITEM_WORDS;
+                            for (int b = 0; b < gone; b += WAVE) {
+                                const int idx = b + (int)lane;
+                                if (idx < gone) {
+                                    Entry x = pool_load(bot + idx);
+                                    x.ks = (x.ks & 255u) | ((uint32_t)sh << 8);
+                                    store_entry(item0 + (int64_t)(idx % ni) * ITEM_WORDS, WAVE, idx / ni, x);
+                                }
+                            }
+                            for (int t = (int)lane; t < ni; t += WAVE)
+                                item0[(int64_t)t * ITEM_WORDS + POOL_FIELDS * WAVE] = (uint32_t)((gone - t + ni - 1) / ni);
+                            bot += gone;
+                            lo = max(lo, bot);
+                            if ((int)lane == q) S.live -= gone;
+                        }
+                    }
+                    // no room for items: the wave finishes the shower itself
+                    if (gone == 0 && lane == 0) sub_l[SL_EXPAND] = 0u;
+                } else if (no_new && et >= 0 && top - bot >= et + WAVE) {
                     if (bot < lo) __threadfence_block();
                     const Entry e = pool_load(bot + (int)lane);
                     const int es = (int)(e.ks >> 8);
@@ -995,21 +1072,18 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
                 // one party of a shared shower is done: its tallies go to the
                 // share; the last party writes the shower's results
                 const int shs = slot_get(S.sh, s);
+                // (one atomic instruction, a field per lane; it is complete
+                // before the party signs off)
+                const uint32_t f = lane + (uint32_t)SH_NODES;
+                const uint32_t v = f == SH_NODES ? (TREE ? 0u : (uint32_t)nn) : f == SH_HITS ? (uint32_t)nh
+                                 : f == SH_PASSES ? (uint32_t)npass : f == SH_ESC ? (uint32_t)nesc
+                                 : f == SH_BACK ? (uint32_t)nback : f == SH_EESC ? eesc
+                                 : f == SH_ECUT ? e_cut : f == SH_ESTOP ? e_stop : 0u;
+                if (f < (uint32_t)SH_OUT && v) atomicAdd(share_ptr(shs, (int)f), v);
+                wait_vmem();
                 uint32_t last_party = 0;
-                if (lane == 0) {
-                    atomicAdd(share_ptr(shs, SH_HITS), (uint32_t)nh);
-                    if (!TREE) atomicAdd(share_ptr(shs, SH_NODES), (uint32_t)nn);
-                    atomicAdd(share_ptr(shs, SH_PASSES), (uint32_t)npass);
-                    atomicAdd(share_ptr(shs, SH_ESC), (uint32_t)nesc);
-                    atomicAdd(share_ptr(shs, SH_BACK), (uint32_t)nback);
-                    atomicAdd(share_ptr(shs, SH_EESC), eesc);
-                    atomicAdd(share_ptr(shs, SH_ECUT), e_cut);
-                    atomicAdd(share_ptr(shs, SH_ESTOP), e_stop);
-                    __threadfence();
-                    last_party = atomicSub(share_ptr(shs, SH_OUT), 1u) == 1u ? 1u : 0u;
-                }
+                if (lane == 0) last_party = atomicSub(share_ptr(shs, SH_OUT), 1u) == 1u ? 1u : 0u;
                 if (__builtin_amdgcn_readfirstlane((int)last_party)) {
-                    __threadfence();
                     const uint32_t v = (int)lane < SH_FIELDS ? share_load(shs, (int)lane) : 0u;
                     const int fi = __builtin_amdgcn_readlane((int)v, SH_I);
                     const int fnn = __builtin_amdgcn_readlane((int)v, SH_NODES);

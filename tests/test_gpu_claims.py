@@ -43,3 +43,28 @@ def test_few_waves_and_sub_batches(waves_per_cu, sub_batches):
     sim = supa.Simulator(geom, supa.OUT_HITS | supa.OUT_KEYS, waves_per_cu=waves_per_cu, sub_batches=sub_batches)
     out = parity.to_numpy(sim.simulate(dev_t(e0), dev_t(pol), dev_t(az), w.seed))
     parity.check_all(out, O.simulate(geom, e0, pol, az, w.seed), geom)
+
+
+@pytest.mark.parametrize("n,e,planes", [(1, 1000.0, 20), (3, 900.0, 9), (63, 300.0, 12), (130, 250.0, 20), (600, 60.0, 20),
+                                        (1024, 40.0, 8)])
+def test_dealt_out_showers(n, e, planes):
+    """Automatic subtree items: showers dealt out at 256 pending particles
+    (and those that never reach them), few planes, 1 to 1,024 showers."""
+    w = workloads.WORKLOADS["loge1to1000_20planes_1m"]
+    geom = workloads.geometry(w, n_planes=planes)
+    _, pol, az = workloads.initial_conditions(w, n)
+    e0 = np.full(n, e, np.float32)
+    e0[::7] *= 0.05
+    print(f"claims: items, {n} showers of {e}, {planes} planes", flush=True)
+    ref = O.simulate(geom, e0, pol, az, 11)
+    for outputs in (supa.OUT_HITS | supa.OUT_TREE | supa.OUT_KEYS, supa.OUT_HITS | supa.OUT_KEYS, 0):
+        sim = supa.Simulator(geom, outputs)
+        out = parity.to_numpy(sim.simulate(dev_t(e0), dev_t(pol), dev_t(az), 11))
+        parity.check_counts(out, ref)
+        if outputs:
+            parity.check_all(out, ref, geom, tree=bool(outputs & supa.OUT_TREE))
+        items = sim.subtree_counts()["items"][0]
+        if planes <= 8:
+            assert items == 0
+        if planes == 20 and e0.max() >= 250.0:
+            assert items > 0
