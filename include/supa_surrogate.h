@@ -192,6 +192,29 @@ supa_status supa_mlp_forward_fused(void *hip_stream, int B, int k_in, int n_hidd
  */
 supa_status supa_mlp_fused_weights(void *hip_stream, int in, int out, const float *W, int permute, uint16_t *wt);
 
+/*
+ * One training step of the network in seven launches: hidden layers (n_hidden
+ * = 1..8 of 256 units, GELU) on k_in inputs (x bf16 [B][ldx]; k_in a multiple
+ * of 16 up to 256), n_out = 2 D outputs (a multiple of 8: means, then
+ * log-variances), the loss and its gradient as supa_nll_grad defines them
+ * (targets y_scale img / e0, img float [B][D]), backward and Adam as
+ * supa_adam (step counts from 1).  The same values as the layer-by-layer
+ * products up to the order of the float sums: bf16 weights, activations,
+ * pre-activations and gradients, float32 sums, exact GELU; the [B][2D] output
+ * itself is not kept.  weights, bias, weights_bf16 (row-major [in][out],
+ * refreshed): host arrays of device pointers, one per layer; moments: four per
+ * layer (m and v of the weights, m and v of the bias).  *loss (device) has the
+ * loss sum added.  B a multiple of 8; every pointer 16-byte aligned but e0's
+ * and loss.  work: device, at least supa_mlp_train_workspace_bytes (-1 for
+ * sizes this entry does not take).
+ */
+int64_t supa_mlp_train_workspace_bytes(int B, int k_in, int n_hidden, int n_out);
+supa_status supa_mlp_train_step(void *hip_stream, int B, int k_in, int n_hidden, int n_out, const uint16_t *x,
+                                int ldx, const float *img, const float *e0, float y_scale, float s_clamp,
+                                int mse_mean, float *const *weights, float *const *bias,
+                                uint16_t *const *weights_bf16, float *const *moments, float lr, float b1, float b2,
+                                float eps, int step, float *loss, void *work, int64_t work_bytes);
+
 /* y[c][r] = bf16(x[r][c]): float [rows][cols] to bf16 [cols][rows] (round to nearest even). */
 supa_status supa_transpose_to_bf16(void *hip_stream, int rows, int cols, const float *x, uint16_t *y);
 

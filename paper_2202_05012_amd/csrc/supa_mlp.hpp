@@ -42,4 +42,33 @@ struct MlpFusedArgs {
     int ldh;
 };
 
+// Arguments of a training step (supa_train.hip): n_hidden layers of 256 on
+// k_in inputs, 2 D outputs (means, then log-variances); layer l of 0 ..
+// n_hidden maps its input (x, or activations act[l - 1]) to the next.
+struct TrainArgs {
+    int B, n_hidden, k_in, D;
+    const uint16_t *x;                                  // bf16 [B][ldx]
+    int ldx;
+    const float *img, *e0;                              // targets y_scale img / e0: [B][D], [B]
+    float y_scale, s_clamp;
+    int mse_mean;
+    float lr, b1, b2, eps, c1, c2;                      // Adam (c1, c2: bias corrections)
+    float *loss;                                        // the loss sum is added here
+    const uint16_t *wb[MLP_FUSED_MAX_HIDDEN + 1];       // bf16 weights [in][out]
+    uint16_t *wb_out[MLP_FUSED_MAX_HIDDEN + 1];         // the same, refreshed by Adam
+    const float *bias[MLP_FUSED_MAX_HIDDEN + 1];
+    float *p_w[MLP_FUSED_MAX_HIDDEN + 1], *m_w[MLP_FUSED_MAX_HIDDEN + 1], *v_w[MLP_FUSED_MAX_HIDDEN + 1];
+    float *p_b[MLP_FUSED_MAX_HIDDEN + 1], *m_b[MLP_FUSED_MAX_HIDDEN + 1], *v_b[MLP_FUSED_MAX_HIDDEN + 1];
+    // workspace (train_layout)
+    uint16_t *act[MLP_FUSED_MAX_HIDDEN], *pre[MLP_FUSED_MAX_HIDDEN], *g[MLP_FUSED_MAX_HIDDEN];   // bf16 [B][256]
+    uint16_t *dout;                                     // bf16 [B][ldd], 2 D columns, zeros beyond
+    int ldd;
+    uint16_t *wt[MLP_FUSED_MAX_HIDDEN + 1];             // bf16 weights [out][in]
+    float *dw, *db;                                     // partial sums of the gradients
+    int64_t dw_off[MLP_FUSED_MAX_HIDDEN + 1], db_off[MLP_FUSED_MAX_HIDDEN + 1];
+    int tr_block[MLP_FUSED_MAX_HIDDEN + 2];             // first transpose block of each layer
+    int wg_tiles[MLP_FUSED_MAX_HIDDEN + 1], wg_parts[MLP_FUSED_MAX_HIDDEN + 1], wg_rows[MLP_FUSED_MAX_HIDDEN + 1];
+    int ad_block[2 * (MLP_FUSED_MAX_HIDDEN + 1) + 1];   // first Adam block of each tensor (W, b per layer)
+};
+
 }  // namespace supa

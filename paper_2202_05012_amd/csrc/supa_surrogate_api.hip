@@ -42,6 +42,8 @@ hipError_t launch_gate_fused(int B, int K, int D, int L, const uint16_t *h, int 
 hipError_t launch_transpose_bf16(int rows, int cols, const float *x, uint16_t *y, hipStream_t s);
 hipError_t launch_mlp_fused(const MlpFusedArgs &a, hipStream_t s);
 hipError_t launch_mlp_weights(int in, int out, const float *W, int permute, uint16_t *wt, hipStream_t s);
+size_t train_layout(TrainArgs &a, char *base);
+hipError_t launch_train(const TrainArgs &a, hipStream_t s);
 size_t sort_work_bytes(int64_t n, int cols);
 hipError_t launch_sort_columns(const float *x, int64_t ld, int64_t n, int cols, void *work, uint32_t **sorted,
                                hipStream_t s);
@@ -363,4 +365,68 @@ extern "C" supa_status supa_occupied_counts(void *stream, int64_t rows, int32_t 
     if (rows == 0) return SUPA_OK;
     if (!img || !cnt) return bad("occupied counts: NULL array");
     return dev(supa::launch_occupied_counts(rows, L, g, img, thr, cnt, (hipStream_t)stream), "occupied counts");
+}
+
+static bool train_shape(int B, int k_in, int n_hidden, int n_out) {
+    return B >= 8 && B % 8 == 0 && B <= 1 << 24 && n_hidden >= 1 && n_hidden <= supa::MLP_FUSED_MAX_HIDDEN && k_in >= 16 &&
+           k_in % 16 == 0 && k_in <= 256 && n_out >= 8 && n_out % 8 == 0 && n_out <= 1 << 20;
+}
+
+extern "C" int64_t supa_mlp_train_workspace_bytes(int B, int k_in, int n_hidden, int n_out) {
+    if (!train_shape(B, k_in, n_hidden, n_out)) return -1;
+    supa::TrainArgs a{};
+    a.B = B;
+    a.k_in = k_in;
+    a.n_hidden = n_hidden;
+    a.D = n_out / 2;
+    return (int64_t)supa::train_layout(a, nullptr);
+}
+
+extern "C" supa_status supa_mlp_train_step(void *stream, int B, int k_in, int n_hidden, int n_out, const uint16_t *x,
+                                           int ldx, const float *img, const float *e0, float y_scale, float s_clamp,
+                                           int mse_mean, float *const *weights, float *const *bias,
+                                           uint16_t *const *weights_bf16, float *const *moments, float lr, float b1,
+                                           float b2, float eps, int step, float *loss, void *work, int64_t work_bytes) {
+    if (!train_shape(B, k_in, n_hidden, n_out))
+        return bad("need 1..8 hidden layers of 256, inputs a multiple of 16 up to 256, rows and outputs multiples of 8");
+    if (!x || !img || !e0 || !weights || !bias || !weights_bf16 || !moments || !loss || !work) return bad("NULL argument");
+    if (ldx < k_in || ldx % 8) return bad("bad leading dimension");
+    if (step < 1) return bad("step counts from 1");
+    auto off16 = [](const void *p) { return p == nullptr || ((uintptr_t)p & 15) != 0; };
+    supa::TrainArgs a{};
+    a.B = B;
+    a.k_in = k_in;
+    a.n_hidden = n_hidden;
+    a.D = n_out / 2;
+    if (off16(x) || off16(img) || off16(work)) return bad("x, img and work must be 16-byte aligned");
+    if (work_bytes < (int64_t)supa::train_layout(a, (char *)work)) return bad("workspace too small");
+    for (int l = 0; l <= n_hidden; ++l) {
+        if (off16(weights[l]) || off16(bias[l]) || off16(weights_bf16[l])) return bad("weights and biases must be 16-byte aligned");
+        for (int q = 0; q < 4; ++q)
+            if (off16(moments[4 * l + q])) return bad("moments must be 16-byte aligned");
+        a.p_w[l] = weights[l];
+        a.p_b[l] = bias[l];
+        a.bias[l] = bias[l];
+        a.wb[l] = weights_bf16[l];
+        a.wb_out[l] = weights_bf16[l];
+        a.m_w[l] = moments[4 * l];
+        a.v_w[l] = moments[4 * l + 1];
+        a.m_b[l] = moments[4 * l + 2];
+        a.v_b[l] = moments[4 * l + 3];
+    }
+    a.x = x;
+    a.ldx = ldx;
+    a.img = img;
+    a.e0 = e0;
+    a.y_scale = y_scale;
+    a.s_clamp = s_clamp;
+    a.mse_mean = mse_mean;
+    a.lr = lr;
+    a.b1 = b1;
+    a.b2 = b2;
+    a.eps = eps;
+    a.c1 = 1.0f - powf(b1, (float)step);
+    a.c2 = 1.0f - powf(b2, (float)step);
+    a.loss = loss;
+    return dev(supa::launch_train(a, (hipStream_t)stream), "train step");
 }

@@ -56,6 +56,7 @@ def _lib():
             "supa_mlp_forward_fused": [vp, i, i, i, vp, i, vp, vp, i, vp, i, vp, i],
             "supa_mlp_fused_weights": [vp, i, i, vp, i, vp],
             "supa_surrogate_last_times": [vp, C.c_int32],
+            "supa_mlp_train_step": [vp, i, i, i, i, vp, i, vp, vp, f, f, i, vp, vp, vp, vp, f, f, f, f, i, vp, vp, i64],
         }
         for name, args in sig.items():
             fn = getattr(L, name)
@@ -65,6 +66,8 @@ def _lib():
             fn = getattr(L, name)
             fn.restype = C.c_int64
             fn.argtypes = [i64, C.c_int32]
+        L.supa_mlp_train_workspace_bytes.restype = C.c_int64
+        L.supa_mlp_train_workspace_bytes.argtypes = [i, i, i, i]
         L.supa_surrogate_last_error.restype = C.c_char_p
         L._surrogate_bound = True
     return L
@@ -414,11 +417,39 @@ class MLP:
             _check(L.supa_adam(_stream(), self.b[l].numel(), _p(self.b[l]), _p(dbs[l]),
                                _p(self.mb[l]), _p(self.vb[l]), None, lr, b1, b2, eps, self.step))
 
+    def _train_bytes(self, x, img):
+        """Workspace bytes of the fused training step (supa_mlp_train_step), or
+        -1 when it does not take this network or batch: hidden layers of 256,
+        and data it can read 16 bytes at a time."""
+        hid = self.dims[1:-1]
+        tensors = [x, img, *self.W, *self.b, *self.Wb, *self.mW, *self.vW, *self.mb, *self.vb]
+        if not hid or any(d != 256 for d in hid) or x.shape[1] != self.dims[0] or x.stride(1) != 1 \
+                or x.stride(0) % 8 or any(t.data_ptr() % 16 for t in tensors):
+            return -1
+        return int(_lib().supa_mlp_train_workspace_bytes(x.shape[0], self.dims[0], len(hid), self.dims[-1]))
+
+    def _train_fused(self, x, img, e0, lr, s_clamp, mse_mean, y_scale, work_bytes, b1=0.9, b2=0.999, eps=1e-8):
+        n, B, n_out = len(self.W), x.shape[0], self.dims[-1]
+        ptrs = lambda ts: (C.c_void_p * len(ts))(*[t.data_ptr() for t in ts])
+        moments = [t for l in range(n) for t in (self.mW[l], self.vW[l], self.mb[l], self.vb[l])]
+        work = torch.empty(work_bytes, dtype=torch.uint8, device=self.device)
+        loss = torch.zeros(1, dtype=torch.float32, device=self.device)
+        _check(_lib().supa_mlp_train_step(_stream(), B, self.dims[0], n - 1, n_out, _p(x), x.stride(0), _p(img), _p(e0),
+                                          y_scale, s_clamp, 1 if mse_mean else 0, ptrs(self.W), ptrs(self.b),
+                                          ptrs(self.Wb), ptrs(moments), lr, b1, b2, eps, self.step + 1, _p(loss),
+                                          _p(work), work_bytes))
+        self.step += 1
+        return loss / (B * (n_out // 2))
+
     def train_step(self, x, img, e0, lr=1e-3, s_clamp=None, mse_mean=True, y_scale=None):
         """One step on targets y_scale * img / e0 (img float [B, D]; default
         scale Y_SCALE); returns the mean NLL.  Means are fitted by squared
         error (mse_mean) or by the NLL, log-variances by the NLL; s_clamp = 0
         holds the log-variances at 0."""
+        work = self._train_bytes(x, img)
+        if work > 0:
+            return self._train_fused(x, img, e0, lr, S_CLAMP if s_clamp is None else s_clamp, mse_mean,
+                                     Y_SCALE if y_scale is None else y_scale, work)
         out, acts, pres = self.forward(x, keep=True)
         B, D2 = out.shape
         dout = torch.empty((B, D2), dtype=torch.int16, device=self.device)

@@ -1,0 +1,84 @@
+"""The fused training step against the layer-by-layer products (forward,
+loss gradient, backward, Adam), which tests/test_gpu_surrogate.py checks
+against the float64 oracle: both round the same quantities to bf16, so they
+differ by the order of float32 sums and by the bf16 values that this moves
+across a rounding boundary.  A sum of up to 10^4 terms is off by about 1e-6,
+so about 1e-6 / 2^-9 = 5e-4 of the bf16 values flip by 2^-8: sqrt(5e-4) 2^-8 =
+9e-5 per tensor and layer.  Bound: 1e-3 in the 2-norm."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2202_05012_amd import surrogate as S
+
+pytestmark = pytest.mark.gpu
+
+
+def data(B, k_in, D, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.zeros(B, k_in, device="cuda")
+    x[:, :min(k_in, 19)] = torch.randn(B, min(k_in, 19), generator=g, device="cuda")
+    e0 = 1.0 + 99.0 * torch.rand(B, generator=g, device="cuda")
+    img = torch.rand(B, D, generator=g, device="cuda") * (torch.rand(B, D, generator=g, device="cuda") < 0.3)
+    return S.to_bf16(x), img * e0[:, None] / 20.0, e0
+
+
+def layer_by_layer(net, x, img, e0, lr, s_clamp, mse_mean, y_scale):
+    out, acts, pres = net.forward(x, keep=True)
+    B, D = out.shape[0], out.shape[1] // 2
+    dout = torch.empty(out.shape, dtype=torch.int16, device="cuda")
+    loss = torch.zeros(1, device="cuda")
+    S._check(S._lib().supa_nll_grad(S._stream(), B, D, S._p(out), S._p(img), S._p(e0), y_scale, s_clamp,
+                                    1 if mse_mean else 0, S._p(dout), S._p(loss)))
+    dWs, dbs = net.backward(acts, pres, dout)
+    net.adam(dWs, dbs, lr=lr)
+    return loss / (B * D)
+
+
+def rel(a, b):
+    a, b = a.double(), b.double()
+    return float((a - b).norm() / max(float(b.norm()), 1e-30))
+
+
+@pytest.mark.parametrize("B,dims,s_clamp,mse_mean", [
+    (8, [32, 256, 40], 20.0, False),                          # one hidden layer, one row block
+    (40, [16, 256, 256, 8], 20.0, True),                      # the fewest inputs and outputs
+    (256, [256, 256, 256, 256, 128], 20.0, True),             # the most inputs, whole tiles
+    (264, [32, 256, 256, 256, 256, 264], 0.5, False),         # ragged bins and rows, clamped log-variances
+    (1032, [32, 256, 256, 256, 256, 1288], 0.0, True),        # several row parts, log-variances held
+    (4104, [32, 256, 256, 256, 256, 10240], 20.0, True),      # the image model, ragged rows
+])
+def test_fused_step_matches_layer_by_layer(B, dims, s_clamp, mse_mean):
+    print(f"train step: batch {B}, layers {dims}", flush=True)
+    D, ys = dims[-1] // 2, 20.0
+    x, img, e0 = data(B, dims[0], D, B)
+    a, b = S.MLP(dims, seed=3), S.MLP(dims, seed=3)
+    assert a._train_bytes(x, img) > 0
+    for net in (a, b):
+        net.step = 100
+        for v in (*net.vW, *net.vb):
+            v.fill_(1e-6)
+    la = a.train_step(x, img, e0, lr=1e-3, s_clamp=s_clamp, mse_mean=mse_mean, y_scale=ys)
+    lb = layer_by_layer(b, x, img, e0, 1e-3, s_clamp, mse_mean, ys)
+    assert a.step == b.step == 101
+    assert rel(la, lb) < 1e-5
+    for l in range(len(dims) - 1):
+        for name in ("mW", "mb", "vW", "vb", "W", "b"):
+            assert rel(getattr(a, name)[l], getattr(b, name)[l]) < 1e-3, (l, name)
+        assert (S.bf16_to_float(a.Wb[l]) - a.W[l]).abs().max() <= a.W[l].abs().max() * 2.0 ** -8
+    if s_clamp == 0.0:                                        # held log-variances have no gradient
+        assert float(a.mb[-1][D:].abs().max()) == 0.0
+
+
+def test_unaligned_and_odd_networks_take_the_general_path():
+    x, img, e0 = data(64, 32, 20, 1)
+    net = S.MLP([32, 256, 40], seed=1)
+    shifted = torch.empty(64 * 20 + 1, device="cuda")[1:].view(64, 20).copy_(img)
+    assert net._train_bytes(x, shifted) < 0
+    assert S.MLP([32, 128, 40], seed=1)._train_bytes(x, img) < 0
+    other = S.MLP([32, 256, 40], seed=1)
+    la, lb = net.train_step(x, img, e0), other.train_step(x, shifted, e0)
+    assert rel(la, lb) < 1e-5
+    with pytest.raises(Exception):
+        net.train_step(x[:60], img[:60], e0[:60])             # 60 rows: not a multiple of 8
+    assert net.step == 1
