@@ -62,7 +62,7 @@ struct TrainArgs {
     // workspace (train_layout)
     uint16_t *act[MLP_FUSED_MAX_HIDDEN], *pre[MLP_FUSED_MAX_HIDDEN], *g[MLP_FUSED_MAX_HIDDEN];   // bf16 [B][256]
     uint16_t *dout;                                     // bf16 [B][ldd], 2 D columns, zeros beyond
-    int ldd;
+    int ldd, Bp;                                        // Bp: rows of the gradients (B up to whole steps)
     uint16_t *wt[MLP_FUSED_MAX_HIDDEN + 1];             // bf16 weights [out][in]
     float *dw, *db;                                     // partial sums of the gradients
     int64_t dw_off[MLP_FUSED_MAX_HIDDEN + 1], db_off[MLP_FUSED_MAX_HIDDEN + 1];

@@ -72,12 +72,20 @@ __device__ __forceinline__ floatx16_t mfma32(u32x4_t a, u32x4_t b, floatx16_t c)
                                                     0, 0, 0);
 }
 
-// A wave's memory operations so far but its latest N vector ones are done, and
-// every wave of the workgroup has got here.  (__syncthreads waits for all of
-// them, stores included.)
+// All but this wave's latest N vector memory operations are done.  (The
+// builtin, not inline assembly: the compiler then knows that copies into LDS
+// have landed and adds no wait of its own before the tile is read.)
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
+
+// The same, and every wave of the workgroup has got here.  (__syncthreads
+// waits for all of a wave's operations, stores included.)
 template <int N>
 __device__ __forceinline__ void meet() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+    wait_vm<N>();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 constexpr floatx16_t kZero16 = {};
@@ -258,7 +266,8 @@ __device__ __forceinline__ float ft_loss(const TrainArgs &a, int t, const FtTile
         }
     // the targets and the next tile's copies have arrived (before this tile's
     // stores are issued, which nobody waits for at the tile's end)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    wait_vm<0>();
+    asm volatile("" ::: "memory");
     float l = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -283,11 +292,12 @@ __device__ __forceinline__ float ft_loss(const TrainArgs &a, int t, const FtTile
                 dm[q] = -r * (a.mse_mean ? 1.0f : ie) * inv_n;
                 ds[q] = fabsf(sr) <= a.s_clamp ? 0.5f * (1.0f - e2) * inv_n : 0.0f;
             }
-            if (m < a.B && bin < a.D) {
-                l += lj;
+            if (m < a.Bp && bin < a.D) {             // rows past the batch: zeros
+                const bool in = m < a.B;
+                l += in ? lj : 0.0f;
                 uint16_t *d = a.dout + (int64_t)m * a.ldd + bin;
-                *(uint2 *)d = make_uint2(pack2(dm[0], dm[1]), pack2(dm[2], dm[3]));
-                *(uint2 *)(d + a.D) = make_uint2(pack2(ds[0], ds[1]), pack2(ds[2], ds[3]));
+                *(uint2 *)d = make_uint2(in ? pack2(dm[0], dm[1]) : 0u, in ? pack2(dm[2], dm[3]) : 0u);
+                *(uint2 *)(d + a.D) = make_uint2(in ? pack2(ds[0], ds[1]) : 0u, in ? pack2(ds[2], ds[3]) : 0u);
             }
         }
     }
@@ -417,25 +427,29 @@ __global__ void __launch_bounds__(512) train_input_grad_kernel(TrainArgs p) {
     const int wk = (wave & 3) * 32, wm = (wave >> 2) * 32;
     const int steps = (2 * p.D + XG_STEP - 1) / XG_STEP;
     floatx4_t acc[2][2] = {{kZero4, kZero4}, {kZero4, kZero4}};
-    xg_issue(p, m0, k0, 0, T0, wave, lane);
-    if (steps > 1) xg_issue(p, m0, k0, 1, T1, wave, lane);
-    if (steps > 2) xg_issue(p, m0, k0, 2, T2, wave, lane);
     // step s: this wave's copies of it have landed once at most those of the
     // two later steps (three instructions each) are outstanding; after the
-    // barrier everyone's have, and everyone has left the buffer of step s - 1
+    // barrier everyone's have, and everyone has left the buffer of step s - 1.
+    // Every stage of the main loop issues (past the end the last step again):
+    // with a condition around it the compiler waits for everything.
 #define XG_STAGE(S, CUR, FREE)                                                    \
-    if ((S) < steps) {                                                            \
-        if ((S) + 2 < steps) meet<6>();                                           \
-        else meet<0>();                                                           \
-        if ((S) + 3 < steps) xg_issue(p, m0, k0, (S) + 3, FREE, wave, lane);      \
-        xg_step(CUR, acc, wk, wm, lc, lq);                                        \
-    }
-    for (int s = 0; s < steps; s += 4) {
+    meet<6>();                                                                    \
+    xg_issue(p, m0, k0, min((S) + 3, steps - 1), FREE, wave, lane);               \
+    xg_step(CUR, acc, wk, wm, lc, lq);
+    xg_issue(p, m0, k0, 0, T0, wave, lane);
+    xg_issue(p, m0, k0, min(1, steps - 1), T1, wave, lane);
+    xg_issue(p, m0, k0, min(2, steps - 1), T2, wave, lane);
+    int s = 0;
+    for (; s + 4 <= steps; s += 4) {
         XG_STAGE(s, T0, T3)
         XG_STAGE(s + 1, T1, T0)
         XG_STAGE(s + 2, T2, T1)
         XG_STAGE(s + 3, T3, T2)
     }
+    meet<0>();
+    if (s < steps) xg_step(T0, acc, wk, wm, lc, lq);
+    if (s + 1 < steps) xg_step(T1, acc, wk, wm, lc, lq);
+    if (s + 2 < steps) xg_step(T2, acc, wk, wm, lc, lq);
 #undef XG_STAGE
     const int H = p.n_hidden;
 #pragma unroll
@@ -443,11 +457,14 @@ __global__ void __launch_bounds__(512) train_input_grad_kernel(TrainArgs p) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int m = m0 + wm + 16 * j + lc, f = k0 + wk + 16 * i + 4 * lq;
-            if (m >= p.B) continue;
-            const uint2 pv = *(const uint2 *)(p.pre[H - 1] + (int64_t)m * W + f);
-            *(uint2 *)(p.g[H - 1] + (int64_t)m * W + f) = make_uint2(
-                pack2(acc[i][j][0] * gelu_slope(bf_to_f(pv.x & 0xffffu)), acc[i][j][1] * gelu_slope(bf_to_f(pv.x >> 16))),
-                pack2(acc[i][j][2] * gelu_slope(bf_to_f(pv.y & 0xffffu)), acc[i][j][3] * gelu_slope(bf_to_f(pv.y >> 16))));
+            uint2 gv = make_uint2(0u, 0u);           // rows past the batch: zeros
+            if (m < p.B) {
+                const uint2 pv = *(const uint2 *)(p.pre[H - 1] + (int64_t)m * W + f);
+                gv = make_uint2(
+                    pack2(acc[i][j][0] * gelu_slope(bf_to_f(pv.x & 0xffffu)), acc[i][j][1] * gelu_slope(bf_to_f(pv.x >> 16))),
+                    pack2(acc[i][j][2] * gelu_slope(bf_to_f(pv.y & 0xffffu)), acc[i][j][3] * gelu_slope(bf_to_f(pv.y >> 16))));
+            }
+            *(uint2 *)(p.g[H - 1] + (int64_t)m * W + f) = gv;
         }
 }
 
@@ -498,8 +515,8 @@ __global__ void __launch_bounds__(512) train_backward_kernel(TrainArgs a) {
                                           acc[i][j][1] * gelu_slope(bf_to_f(pv.x >> 16))),
                                     pack2(acc[i][j][2] * gelu_slope(bf_to_f(pv.y & 0xffffu)),
                                           acc[i][j][3] * gelu_slope(bf_to_f(pv.y >> 16))));
-                    *(uint2 *)(a.g[l - 1] + (int64_t)m * W + f) = gv;
                 }
+                *(uint2 *)(a.g[l - 1] + (int64_t)m * W + f) = gv;          // (zeros past the batch)
                 *(uint2 *)&Xo[lc + 16 * j][f] = gv;
             }
         __syncthreads();
@@ -519,47 +536,37 @@ __global__ void __launch_bounds__(512) train_backward_kernel(TrainArgs a) {
 // Both operands are stored rows first, so the reduction runs across rows of
 // the LDS tiles: ds_read_b64_tr_b16 hands each lane four rows of its column
 // (two reads make an operand), which replaces a transposing store of single
-// bf16.  Chunk c of row m sits at c ^ f(m), f = 2 (m & 3) + ((m >> 2) & 1):
-// the four rows of a transposing read fall on different banks.  The bias
-// gradients are summed from the staged chunks on the way into LDS.
+// bf16.  Chunk c of row m sits at c ^ tr_swizzle(m): the four rows of a
+// transposing read fall on different banks.  K steps of 64 rows are copied
+// straight into LDS two steps ahead in three buffers (a step takes less time
+// than a load from memory).  Gradient rows past the batch are zeros (their
+// producers write them), so whatever stands beside them adds nothing; columns
+// past a layer's inputs or outputs repeat others and are not stored.  The
+// bias gradients are summed from the gradient tiles in passing.
 // ---------------------------------------------------------------------------
 constexpr int WG_N = 128, WG_K = 64;
 
-struct WgRegs {
-    u32x4_t a[4], g[2];
+struct WgTile {
+    char a[WG_K * 512], g[WG_K * 256];
 };
 
 struct WgJob {
     const uint16_t *act, *g;
-    int lda, ldg, in, out, n0, m_begin, m_end;
+    int lda, ldg, in, out, n0;
 };
 
-__device__ __forceinline__ void wg_load(const WgJob &J, int m0, WgRegs &R) {
-    const u32x4_t z = {0u, 0u, 0u, 0u};
+__device__ __forceinline__ void wg_issue(const WgJob &J, int B, int m0, WgTile &T, int wave, int lane) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {                      // 64 rows x 32 chunks
-        const int c = (int)threadIdx.x + 512 * r, m = m0 + (c >> 5), k = (c & 31) * 8;
-        R.a[r] = m < J.m_end && k < J.in ? *(const u32x4_t *)(J.act + (int64_t)m * J.lda + k) : z;
+    for (int q = 0; q < 4; ++q) {                      // two rows of activations per instruction
+        const int blk = 4 * wave + q, m = 2 * blk + (lane >> 5), k = 8 * ((lane & 31) ^ tr_swizzle(m));
+        const uint16_t *src = J.act + (int64_t)min(m0 + m, B - 1) * J.lda + (k < J.in ? k : 0);
+        __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)(&T.a[0] + 1024 * blk), 16, 0, 0);
     }
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {                      // 64 rows x 16 chunks
-        const int c = (int)threadIdx.x + 512 * r, m = m0 + (c >> 4), n = J.n0 + (c & 15) * 8;
-        R.g[r] = m < J.m_end && n < J.out ? *(const u32x4_t *)(J.g + (int64_t)m * J.ldg + n) : z;
-    }
-}
-
-__device__ __forceinline__ int wg_f(int m) { return ((m & 3) << 1) | ((m >> 2) & 1); }
-
-__device__ __forceinline__ void wg_store(const WgRegs &R, char *A, char *G) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int c = (int)threadIdx.x + 512 * r, m = c >> 5;
-        *(u32x4_t *)(A + 512 * m + 16 * ((c & 31) ^ wg_f(m))) = R.a[r];
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int c = (int)threadIdx.x + 512 * r, m = c >> 4;
-        *(u32x4_t *)(G + 256 * m + 16 * ((c & 15) ^ wg_f(m))) = R.g[r];
+    for (int q = 0; q < 2; ++q) {                      // four rows of the gradient
+        const int blk = 2 * wave + q, m = 4 * blk + (lane >> 4), n = J.n0 + 8 * ((lane & 15) ^ tr_swizzle(m));
+        const uint16_t *src = J.g + (int64_t)(m0 + m) * J.ldg + (n < J.out ? n : 0);
+        __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)(&T.g[0] + 1024 * blk), 16, 0, 0);
     }
 }
 
@@ -573,15 +580,45 @@ __device__ __forceinline__ u32x4_t wg_operand(char *T, int col0, int kk, int lan
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int m = 16 * kk + 8 * lh + 4 * h + j;
-        v[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(T + PB * m + 16 * (c ^ ((j << 1) | h)) + 8 * (lane & 1)));
+        // (one offset: the compiler follows few steps back to the LDS variable, and
+        // reads it cannot place wait for every copy in flight)
+        const int at = PB * m + 16 * (c ^ ((j << 1) | h)) + 8 * (lane & 1);
+        v[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(T + at));
     }
     struct { short4_t a, b; } two = {v[0], v[1]};
     return __builtin_bit_cast(u32x4_t, two);
 }
 
+__device__ __forceinline__ void wg_step(WgTile &T, floatx16_t (&acc)[2][2], float (&bs)[8], int wk, int wn, int lane) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        u32x4_t x[2], y[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x[i] = wg_operand<512>(&T.a[0], wk + 32 * i, kk, lane);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) y[j] = wg_operand<256>(&T.g[0], wn + 32 * j, kk, lane);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = mfma32(x[i], y[j], acc[i][j]);
+    }
+    // bias: this thread's chunk (of 16) of two rows
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int m = ((int)threadIdx.x >> 4) + 32 * r;
+        const int at = 256 * m + 16 * (((int)threadIdx.x & 15) ^ tr_swizzle(m));
+        const u32x4_t v = *(const u32x4_t *)(&T.g[0] + at);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            bs[2 * q] += bf_to_f(v[q] & 0xffffu);
+            bs[2 * q + 1] += bf_to_f(v[q] >> 16);
+        }
+    }
+}
+
 __global__ void __launch_bounds__(512) train_weight_grad_kernel(TrainArgs a) {
-    __shared__ __attribute__((aligned(16))) char A[2][WG_K * 512], G[2][WG_K * 256];
-    __shared__ float bsum[32][WG_N + 4];
+    __shared__ __attribute__((aligned(1024))) WgTile T0, T1, T2;
+    __shared__ __attribute__((aligned(16))) float bsum[32][WG_N];      // 160 KB with the tiles: all of a CU's LDS
     // the output layer's blocks first (the longest), then the others
     int l = a.n_hidden;
     int b = blockIdx.x;
@@ -595,56 +632,34 @@ __global__ void __launch_bounds__(512) train_weight_grad_kernel(TrainArgs a) {
     J.g = l == a.n_hidden ? a.dout : a.g[l];
     J.ldg = l == a.n_hidden ? a.ldd : W;
     J.n0 = tile * WG_N;
-    J.m_begin = part * a.wg_rows[l];
-    J.m_end = min(a.B, J.m_begin + a.wg_rows[l]);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lc = lane & 31, lh = lane >> 5;
+    const int m_begin = part * a.wg_rows[l], m_end = min(a.B, m_begin + a.wg_rows[l]);
+    const int steps = (m_end - m_begin + WG_K - 1) / WG_K;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, lc = lane & 31, lh = lane >> 5;
     const int wk = (wave >> 1) * 64, wn = (wave & 1) * 64;
-    const bool use = wk < J.in;            // the first layer has few inputs
     floatx16_t acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = kZero16;
     float bs[8] = {};
-    WgRegs R;
-    auto bias_add = [&]() {
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                bs[2 * q] += bf_to_f(R.g[r][q] & 0xffffu);
-                bs[2 * q + 1] += bf_to_f(R.g[r][q] >> 16);
-            }
-    };
-    wg_load(J, J.m_begin, R);
-    bias_add();
-    wg_store(R, A[0], G[0]);
-    __syncthreads();
-    int cur = 0;
-    for (int m0 = J.m_begin; m0 < J.m_end; m0 += WG_K) {
-        const bool more = m0 + WG_K < J.m_end;
-        if (more) wg_load(J, m0 + WG_K, R);
-        if (use) {
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                u32x4_t x[2], y[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) x[i] = wg_operand<512>(A[cur], wk + 32 * i, kk, lane);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) y[j] = wg_operand<256>(G[cur], wn + 32 * j, kk, lane);
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) acc[i][j] = mfma32(x[i], y[j], acc[i][j]);
-            }
-        }
-        if (more) {
-            bias_add();
-            wg_store(R, A[cur ^ 1], G[cur ^ 1]);
-        }
-        __syncthreads();
-        cur ^= 1;
+    // (see train_input_grad_kernel; six copy instructions per wave and step)
+#define WG_STAGE(S, CUR, FREE)                                                            \
+    meet<6>();                                                                            \
+    wg_issue(J, a.B, m_begin + WG_K * min((S) + 2, steps - 1), FREE, wave, lane);         \
+    wg_step(CUR, acc, bs, wk, wn, lane);
+    wg_issue(J, a.B, m_begin, T0, wave, lane);
+    wg_issue(J, a.B, m_begin + WG_K * min(1, steps - 1), T1, wave, lane);
+    int s = 0;
+    for (; s + 3 <= steps; s += 3) {
+        WG_STAGE(s, T0, T2)
+        WG_STAGE(s + 1, T1, T0)
+        WG_STAGE(s + 2, T2, T1)
     }
+    meet<0>();
+    if (s < steps) wg_step(T0, acc, bs, wk, wn, lane);
+    if (s + 1 < steps) wg_step(T1, acc, bs, wk, wn, lane);
+#undef WG_STAGE
     float *out = a.dw + a.dw_off[l] + (int64_t)part * J.in * J.out;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -655,14 +670,15 @@ __global__ void __launch_bounds__(512) train_weight_grad_kernel(TrainArgs a) {
                 const int k = wk + 32 * i + 8 * (r >> 2) + 4 * lh + (r & 3), n = J.n0 + wn + 32 * j + lc;
                 if (k < J.in && n < J.out) out[(int64_t)k * J.out + n] = acc[i][j][r];
             }
-    // bias: thread t holds the sums of chunk t & 15 over its rows (t >> 4 of each 32)
+    // bias: thread t holds the sums of chunk t & 15 over rows t >> 4 (of each
+    // 32)
     *(floatx4_t *)&bsum[threadIdx.x >> 4][8 * (threadIdx.x & 15)] = floatx4_t{bs[0], bs[1], bs[2], bs[3]};
     *(floatx4_t *)&bsum[threadIdx.x >> 4][8 * (threadIdx.x & 15) + 4] = floatx4_t{bs[4], bs[5], bs[6], bs[7]};
     __syncthreads();
     if (threadIdx.x < WG_N && J.n0 + (int)threadIdx.x < J.out) {
-        float s = 0.0f;
-        for (int q = 0; q < 32; ++q) s += bsum[q][threadIdx.x];
-        a.db[a.db_off[l] + (int64_t)part * J.out + J.n0 + threadIdx.x] = s;
+        float t = 0.0f;
+        for (int q = 0; q < 32; ++q) t += bsum[q][threadIdx.x];
+        a.db[a.db_off[l] + (int64_t)part * J.out + J.n0 + threadIdx.x] = t;
     }
 }
 
@@ -712,17 +728,20 @@ size_t train_layout(TrainArgs &a, char *base) {
     };
     const int H = a.n_hidden;
     const int64_t N = 2 * (int64_t)a.D;
+    // gradient rows up to whole K steps of the weight gradients (zeros past the batch)
+    a.Bp = (a.B + WG_K - 1) / WG_K * WG_K;
+    const size_t rows = (size_t)a.Bp;
     for (int l = 0; l < H; ++l) {
         a.act[l] = (uint16_t *)take((size_t)a.B * W * 2);
         a.pre[l] = (uint16_t *)take((size_t)a.B * W * 2);
-        a.g[l] = (uint16_t *)take((size_t)a.B * W * 2);
+        a.g[l] = (uint16_t *)take(rows * W * 2);
     }
     // rows of the gradient: whole K steps, and an odd number of 256-byte units
     // when they are long, so that equal columns of consecutive rows lie in
     // different L2 channels (at 20 KB, a multiple of 4 KB, all in one)
     a.ldd = (int)((N + XG_STEP - 1) / XG_STEP * XG_STEP);
     if (a.ldd >= 1024) a.ldd = ((a.ldd + 127) / 128 | 1) * 128;
-    a.dout = (uint16_t *)take((size_t)a.B * a.ldd * 2);
+    a.dout = (uint16_t *)take(rows * a.ldd * 2);
     int64_t off_w = 0, off_b = 0;
     int tr = 0, ad = 0;
     for (int l = 0; l <= H; ++l) {
@@ -762,7 +781,7 @@ hipError_t launch_train(const TrainArgs &a, hipStream_t s) {
     const int split = std::max(1, std::min(tiles, (256 + rb - 1) / rb)), per = (tiles + split - 1) / split;
     hipLaunchKernelGGL(train_final_kernel, dim3(rb, (tiles + per - 1) / per), dim3(512), 0, s, a, per);
     hipLaunchKernelGGL(train_input_grad_kernel, dim3((a.B + XG_M - 1) / XG_M, W / XG_K), dim3(512), 0, s, a);
-    if (H > 1) hipLaunchKernelGGL(train_backward_kernel, dim3((a.B + ROWS - 1) / ROWS), dim3(512), 0, s, a);
+    if (H > 1) hipLaunchKernelGGL(train_backward_kernel, dim3(a.Bp / ROWS), dim3(512), 0, s, a);
     int blocks = 0;
     for (int l = 0; l <= H; ++l) blocks += a.wg_tiles[l] * a.wg_parts[l];
     hipLaunchKernelGGL(train_weight_grad_kernel, dim3(blocks), dim3(512), 0, s, a);
