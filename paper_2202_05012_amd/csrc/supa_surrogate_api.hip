@@ -45,12 +45,12 @@ hipError_t launch_mlp_weights(int in, int out, const float *W, int permute, uint
 size_t train_layout(TrainArgs &a, char *base);
 hipError_t launch_train(const TrainArgs &a, hipStream_t s);
 size_t sort_work_bytes(int64_t n, int cols);
-hipError_t launch_sort_columns(const float *x, int64_t ld, int64_t n, int cols, void *work, uint32_t **sorted,
-                               hipStream_t s);
-hipError_t launch_w1_sorted(const uint32_t *ka, const uint32_t *kb, int64_t n, int cols, double *part, double *w1,
-                            hipStream_t s);
+hipError_t launch_sort_columns(int samples, const float *const *x, const int64_t *ld, int64_t n, int cols, void *work,
+                               uint32_t **sorted, int64_t *stride, hipStream_t s);
+hipError_t launch_w1_sorted(const uint32_t *ka, const uint32_t *kb, int64_t n, int64_t stride, int cols, double *part,
+                            double *w1, hipStream_t s);
 int64_t w1_sorted_partial_words(int64_t n, int cols);
-hipError_t launch_keys_to_floats(const uint32_t *k, int64_t total, float *out, hipStream_t s);
+hipError_t launch_keys_to_floats(const uint32_t *k, int64_t n, int64_t stride, int cols, float *out, hipStream_t s);
 hipError_t launch_occupied_counts(int64_t rows, int L, int g, const float *img, float thr, float *cnt,
                                   hipStream_t s);
 }  // namespace supa
@@ -320,10 +320,13 @@ extern "C" supa_status supa_group_sums(void *stream, int rows, int L, int g, con
 static constexpr int64_t kMaxSortRows = 1LL << 30;
 
 static size_t al256s(size_t b) { return (b + 255) & ~(size_t)255; }
+// room in a sort's workspace to start it on 256 bytes (its kernels read 16 bytes at a time)
+static constexpr int64_t kSortAlign = 256;
+static char *sort_base(void *work) { return (char *)al256s((size_t)(uintptr_t)work); }
 
 extern "C" int64_t supa_sort_columns_workspace_bytes(int64_t n, int32_t cols) {
     if (n < 0 || n > kMaxSortRows || cols < 0 || cols > 4096) return -1;
-    return (int64_t)supa::sort_work_bytes(n, cols);
+    return (int64_t)supa::sort_work_bytes(n, cols) + kSortAlign;
 }
 
 extern "C" supa_status supa_sort_columns(void *stream, int64_t n, int32_t cols, const float *x, int64_t ld,
@@ -331,17 +334,20 @@ extern "C" supa_status supa_sort_columns(void *stream, int64_t n, int32_t cols, 
     if (n < 0 || n > kMaxSortRows || cols < 0 || cols > 4096) return bad("sort: n or cols out of range");
     if (n == 0 || cols == 0) return SUPA_OK;
     if (!x || !out || !work || ld < cols) return bad("sort: NULL array or ld < cols");
-    if (work_bytes < (int64_t)supa::sort_work_bytes(n, cols)) return bad("sort: workspace too small");
+    if (work_bytes < supa_sort_columns_workspace_bytes(n, cols)) return bad("sort: workspace too small");
+    work = sort_base(work);
     uint32_t *sorted = nullptr;
-    supa_status st = dev(supa::launch_sort_columns(x, ld, n, cols, work, &sorted, (hipStream_t)stream), "sort");
+    int64_t stride = 0;
+    supa_status st =
+        dev(supa::launch_sort_columns(1, &x, &ld, n, cols, work, &sorted, &stride, (hipStream_t)stream), "sort");
     if (st != SUPA_OK) return st;
-    return dev(supa::launch_keys_to_floats(sorted, n * cols, out, (hipStream_t)stream), "sorted values");
+    return dev(supa::launch_keys_to_floats(sorted, n, stride, cols, out, (hipStream_t)stream), "sorted values");
 }
 
 extern "C" int64_t supa_w1_equal_workspace_bytes(int64_t n, int32_t cols) {
     if (n < 0 || n > kMaxSortRows || cols < 0 || cols > 4096) return -1;
-    return (int64_t)(2 * al256s(supa::sort_work_bytes(n, cols)) +
-                     al256s((size_t)supa::w1_sorted_partial_words(n, cols) * 8));
+    return (int64_t)(al256s(supa::sort_work_bytes(n, 2 * cols)) +
+                     al256s((size_t)supa::w1_sorted_partial_words(n, cols) * 8)) + kSortAlign;
 }
 
 extern "C" supa_status supa_w1_equal(void *stream, int64_t n, int32_t cols, const float *a, int64_t lda,
@@ -349,13 +355,17 @@ extern "C" supa_status supa_w1_equal(void *stream, int64_t n, int32_t cols, cons
     if (n < 1 || n > kMaxSortRows || cols < 1 || cols > 4096) return bad("w1: n or cols out of range");
     if (!a || !b || !w1 || !work || lda < cols || ldb < cols) return bad("w1: NULL array or leading dimension < cols");
     if (work_bytes < supa_w1_equal_workspace_bytes(n, cols)) return bad("w1: workspace too small");
-    const size_t sw = al256s(supa::sort_work_bytes(n, cols));
-    uint32_t *ka = nullptr, *kb = nullptr;
+    const size_t sw = al256s(supa::sort_work_bytes(n, 2 * cols));
+    work = sort_base(work);
+    uint32_t *k = nullptr;
+    int64_t stride = 0;
     const hipStream_t s = (hipStream_t)stream;
-    supa_status st = dev(supa::launch_sort_columns(a, lda, n, cols, work, &ka, s), "w1 sort a");
-    if (st == SUPA_OK) st = dev(supa::launch_sort_columns(b, ldb, n, cols, (char *)work + sw, &kb, s), "w1 sort b");
+    const float *const x[2] = {a, b};
+    const int64_t ld[2] = {lda, ldb};
+    supa_status st = dev(supa::launch_sort_columns(2, x, ld, n, cols, work, &k, &stride, s), "w1 sort");
     if (st == SUPA_OK)
-        st = dev(supa::launch_w1_sorted(ka, kb, n, cols, (double *)((char *)work + 2 * sw), w1, s), "w1 sums");
+        st = dev(supa::launch_w1_sorted(k, k + cols * stride, n, stride, cols, (double *)((char *)work + sw), w1, s),
+                 "w1 sums");
     return st;
 }
 
