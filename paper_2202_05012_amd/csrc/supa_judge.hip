@@ -197,23 +197,27 @@ __global__ void __launch_bounds__(RS_THREADS) rs_scatter(const uint32_t *keys, i
     }
     uint32_t rank[RS_ITEMS];
     uint32_t *mine = cnt[w];
-    const uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
     for (int r = 0; r < RS_ITEMS; ++r) {
         const bool valid = w * (64 * RS_ITEMS) + 64 * r + lane < m;
         const uint32_t d = (k[r] >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
+        // the lanes of equal digit: per bit, those whose bit is this lane's
+        // (x: the bit in every position; 0x90 = a & ~(b ^ c): four vector
+        // instructions per bit)
+        const uint64_t in = __ballot(valid);
+        uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t q = __ballot(bit);
-            peers &= bit ? q : ~q;
+            const int x = (int)(d << (31 - b)) >> 31;
+            const uint64_t q = __ballot(x < 0);
+            lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)q, (uint32_t)x, 0x90);
+            hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(q >> 32), (uint32_t)x, 0x90);
         }
-        const uint32_t ahead = (uint32_t)__popcll(peers & below);
+        const uint32_t ahead = lanes_below(((uint64_t)hi << 32) | lo);
         const uint32_t prev = mine[d];
         rank[r] = prev + ahead;
         asm volatile("" ::: "memory");             // every lane has read before the first of a digit adds
-        if (valid && ahead == 0u) mine[d] = prev + (uint32_t)__popcll(peers);
+        if (valid && ahead == 0u) mine[d] = prev + (uint32_t)(__popc(lo) + __popc(hi));
         asm volatile("" ::: "memory");
     }
     __syncthreads();
