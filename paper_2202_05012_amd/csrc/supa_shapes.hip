@@ -4,7 +4,8 @@
 // Wasserstein-1 distance between histograms of two samples (section
 // "Performance Analysis of Generative Models").
 //
-// Shape variables: one lane per shower.  A lane streams its shower's segment
+// Shape variables: one wave per shower (below), or, for large batches of few
+// hits per shower, one lane per shower.  Such a lane streams its shower's segment
 // of the hit arrays in aligned blocks of four hits (one 16-byte load per
 // array), keeps the double-precision sums of the layer run it is in, and
 // writes that layer's record when the run ends; lanes take showers from a
@@ -151,13 +152,33 @@ __device__ inline void write_empty_layer(float *rec) {
     rec[SUPA_LV_ENERGY_RATIO] = nan;
 }
 
-// work: [0] showers in error, [1] queue, [2, 4) unused, then the global
-// order's bucket sizes and cursors (ORDER_BUCKETS each), then the order [n].
+// work: [0] showers in error, [1] queue, [2] whether one wave takes a shower
+// (else one lane), [3] unused, then the global order's bucket sizes and cursors
+// (ORDER_BUCKETS each), then the order [n].
 constexpr int ORDER_BUCKETS = 1024;
 constexpr int WORK_HEAD = 4 + 2 * ORDER_BUCKETS;
 
-__global__ void shapes_clear(int32_t *work) {
-    for (int i = threadIdx.x; i < WORK_HEAD; i += blockDim.x) work[i] = 0;
+// Batches of more than WAVE_CALLS showers per CU are summed by one wave per
+// shower when a shower has MIN_WAVE_HITS hits on average, by one lane per
+// shower otherwise (20 layers, 100,000 showers, us by wave / by lane: 941 hits
+// 545 / 800, 94 hits 184 / 220, 47 hits 162 / 141; a million showers of 3 hits
+// 1130 / 285: a wave's fixed work per shower is then all there is).  Smaller
+// batches always by wave: one lane per shower leaves the chip idle (3,000
+// showers of 942 hits 34 / 549, of 47 hits 16 / 86; 10,000 of 9 hits 23 / 33).
+// The average is taken from the ends of the first and last segment, on the
+// device: the arrays may be longer than what is in use.  It decides nothing
+// but the speed.
+constexpr int WAVE_CALLS = 64;
+constexpr int MIN_WAVE_HITS = 64;
+
+__global__ void shapes_clear(int32_t *work, int64_t n, const int64_t *off, const int32_t *cnt, int cstride,
+                             int always) {
+    for (int i = threadIdx.x; i < WORK_HEAD; i += blockDim.x) {
+        int v = 0;
+        if (i == 2 && n > 0)
+            v = always || off[n - 1] + cnt[(size_t)(n - 1) * cstride] - off[0] >= MIN_WAVE_HITS * n ? 1 : 0;
+        work[i] = v;
+    }
 }
 
 // Order in which the lanes take showers: longest first, within windows of
@@ -207,8 +228,10 @@ __device__ inline void bucket_starts(const uint32_t *src, uint32_t *dst, int t) 
 }
 
 __global__ void __launch_bounds__(ORDER_THREADS)
-    shapes_order(int64_t n, int64_t win, const int32_t *cnt, int cstride, int32_t *order) {
+    shapes_order(int64_t n, int64_t win, const int32_t *cnt, int cstride, const int32_t *by_wave,
+                 int32_t *order) {
     __shared__ uint32_t hist[ORDER_BUCKETS];
+    if (*by_wave) return;
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * win;
     const int64_t m = n - base < win ? n - base : win;
@@ -230,8 +253,9 @@ __global__ void __launch_bounds__(ORDER_THREADS)
 constexpr int ORDER_CHUNK = 4 * ORDER_THREADS;  // showers per block of the two passes
 
 __global__ void __launch_bounds__(ORDER_THREADS)
-    shapes_order_sizes(int64_t n, const int32_t *cnt, int cstride, uint32_t *gsize) {
+    shapes_order_sizes(int64_t n, const int32_t *cnt, int cstride, const int32_t *by_wave, uint32_t *gsize) {
     __shared__ uint32_t hist[ORDER_BUCKETS];
+    if (*by_wave) return;
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * ORDER_CHUNK;
     const int64_t m = n - base < ORDER_CHUNK ? n - base : ORDER_CHUNK;
@@ -247,9 +271,10 @@ __global__ void __launch_bounds__(ORDER_THREADS)
 // Pass 2: each block reserves its range of every bucket (gcur, zeroed
 // before) and places its showers.
 __global__ void __launch_bounds__(ORDER_THREADS)
-    shapes_order_place(int64_t n, const int32_t *cnt, int cstride, const uint32_t *gsize, uint32_t *gcur,
-                       int32_t *order) {
+    shapes_order_place(int64_t n, const int32_t *cnt, int cstride, const int32_t *by_wave,
+                       const uint32_t *gsize, uint32_t *gcur, int32_t *order) {
     __shared__ uint32_t hist[ORDER_BUCKETS], start[ORDER_BUCKETS];
+    if (*by_wave) return;
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * ORDER_CHUNK;
     const int64_t m = n - base < ORDER_CHUNK ? n - base : ORDER_CHUNK;
@@ -357,6 +382,7 @@ __device__ inline void ring_drain(Ring &q, int &h, int t, int most, float *lv, i
 __global__ void __launch_bounds__(WAVE) shapes_kernel(ShapeArgs A) {
     __shared__ Ring q;
     extern __shared__ float ef[];
+    if (A.work[2]) return;                // a wave each
     const int lane = threadIdx.x;
     const int L = A.L;
     const float nan = __builtin_nanf("");
@@ -516,6 +542,404 @@ __global__ void __launch_bounds__(WAVE) shapes_kernel(ShapeArgs A) {
         if (work) pos = bad ? end : (b0 + BLK < end ? b0 + BLK : end);
     }
     while (t - h > 0) ring_drain(q, h, t, WAVE, A.lv, L);
+}
+
+// ---------------------------------------------------------------------------
+// One wave per shower.  The segment is read once, coalesced, 256 hits per step
+// (16 bytes per lane and array), hits of layer -1 left out, into an LDS tile
+// of up to SHW_TILE hits.  The tile's layer runs are cut into fragments of
+// about equal length, at most one per lane and never across a run, so that
+// every lane sums hits of one layer only (no test for a change of layer in the
+// loop) and lanes are evenly loaded.  The fragments' sums are then added run
+// by run in order: sixteen lanes walk sixteen fragments, one lane per kind of
+// sum, and the lane that owns the run (run r of the shower: lane r; more than
+// 64 runs repeat a layer) takes at most four partial sums.  Every sum has a
+// fixed order: results do not depend on the batch or on timing.
+//
+// Bound by vector instructions (2,000 per shower of 941 hits in 20 layers,
+// half of them the sums; 80% of the issue slots), next to 1.5 GB of hits:
+// 100,000 such showers 545 us (one lane per shower: 800 us, until the lane
+// with the longest shower was done), 3,000 34 us (549).  768 hits per tile:
+// 10 KB of LDS, four waves per SIMD (1,024: three waves, 570 us; 512: more
+// tiles per shower, 690 us).  Reading the next tile's or shower's first step
+// ahead cost more registers than it hid (605 us).  At most 128 workgroups per
+// CU, striding over the showers: one shower each would be 15 us
+// faster there, but leaving again 100,000 workgroups for nothing when the lanes
+// do the work costs more.
+// ---------------------------------------------------------------------------
+constexpr int SHW_TILE = 768;
+constexpr int SHW_STEP = 4 * WAVE;        // hits read per step
+constexpr int SHW_SUMS = 12;
+constexpr int SHW_LD = WAVE + 2;          // row of 16-byte aligned fragment sums, rows on different banks
+
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+struct WaveTile {
+    union {
+        float hit[3][SHW_TILE + 4];       // x, y, e; entry SHW_TILE is a point of zeros
+        struct {                          // the fragments' sums (once the hits are read)
+            double d[SHW_SUMS][SHW_LD];
+            f32x2 top[WAVE];              // two largest energies
+        } f;
+    };
+    int pos[WAVE + 1], lay[WAVE], flag[WAVE];
+};
+
+// orders LDS accesses of a wave's lanes among each other
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ inline int lanes_below(uint64_t m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
+
+// Data of another lane by DPP, 0 where there is none: shifts by 1, 2, 4, 8
+// within rows of sixteen lanes, then row ends broadcast to the rows above.
+template <int K>
+__device__ inline int scan_src(int v) {
+    if constexpr (K < 4) return __builtin_amdgcn_update_dpp(0, v, 0x110 + (1 << K), 0xf, 0xf, true);
+    if constexpr (K == 4) return __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    return __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+}
+
+template <int K>
+__device__ inline double scan_src(double v) {
+    return __hiloint2double(scan_src<K>(__double2hiint(v)), scan_src<K>(__double2loint(v)));
+}
+
+// sum over lanes 0 .. lane (lane 63: the wave's)
+template <typename T>
+__device__ inline T scan_sum(T v) {
+    v += scan_src<0>(v);
+    v += scan_src<1>(v);
+    v += scan_src<2>(v);
+    v += scan_src<3>(v);
+    v += scan_src<4>(v);
+    v += scan_src<5>(v);
+    return v;
+}
+
+// maximum over the wave of v >= 0
+__device__ inline int wave_max(int v) {
+    v = max(v, scan_src<0>(v));
+    v = max(v, scan_src<1>(v));
+    v = max(v, scan_src<2>(v));
+    v = max(v, scan_src<3>(v));
+    v = max(v, scan_src<4>(v));
+    v = max(v, scan_src<5>(v));
+    return __builtin_amdgcn_readlane(v, WAVE - 1);
+}
+
+__device__ inline double wave_sum(double v) {
+    v = scan_sum(v);
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), WAVE - 1),
+                            __builtin_amdgcn_readlane(__double2loint(v), WAVE - 1));
+}
+
+struct Four {
+    f32x4 x, y, e;
+    i32x4 l;
+};
+
+// This lane's four hits of the step at base: hits 4 lane .. 4 lane + 3 of the
+// `here` hits there (others: any values).  Whole steps inside the arrays are
+// read 16 bytes at a time (hits of the next segment included), only the
+// arrays' end hit by hit.
+__device__ inline Four read_four(const ShapeArgs &A, int64_t base, int here, int lane) {
+    Four h;
+    const float *x = A.x + base, *y = A.y + base, *e = A.e + base;
+    const int32_t *layer = A.layer + base;
+    const unsigned i = 4u * (unsigned)lane;
+    if (base + SHW_STEP <= A.len) {
+        h.x = *(const f32x4u *)(x + i);
+        h.y = *(const f32x4u *)(y + i);
+        h.e = *(const f32x4u *)(e + i);
+        h.l = *(const i32x4u *)(layer + i);
+    } else {
+#pragma unroll
+        for (unsigned u = 0; u < 4; ++u) {
+            const unsigned j = (int)(i + u) < here ? i + u : 0u;
+            h.x[u] = x[j];
+            h.y[u] = y[j];
+            h.e[u] = e[j];
+            h.l[u] = layer[j];
+        }
+    }
+    return h;
+}
+
+// Lanes whose hit u of a step is one of its `here` hits.
+__device__ inline uint64_t lanes_with(int here, int u) {
+    const int k = (here - u + 3) >> 2;
+    return k <= 0 ? 0ull : k >= WAVE ? ~0ull : (1ull << k) - 1ull;
+}
+
+__device__ inline void add_top(float &e1, float &e2, float o1, float o2) {
+    e2 = __builtin_fmaxf(__builtin_fmaxf(e2, o2), __builtin_fminf(e1, o1));
+    e1 = __builtin_fmaxf(e1, o1);
+}
+
+// Adds lane - D's pair when it lies in the same row of sixteen and belongs to the same run.
+template <int D>
+__device__ inline void seg_top(float &e1, float &e2, int run) {
+    const int r = __builtin_amdgcn_update_dpp(-1, run, 0x110 + D, 0xf, 0xf, false);
+    const float o1 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e1), 0x110 + D, 0xf, 0xf, false));
+    const float o2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e2), 0x110 + D, 0xf, 0xf, false));
+    float s1 = e1, s2 = e2;
+    add_top(s1, s2, o1, o2);
+    e1 = r == run ? s1 : e1;
+    e2 = r == run ? s2 : e2;
+}
+
+// Shape variables of shower s.
+__device__ void wave_shower(const ShapeArgs &A, WaveTile &T, int64_t s, int lane) {
+    const int L = A.L;
+    const float nan = __builtin_nanf("");
+    // a segment reaching outside the arrays is the caller's error; never read
+    // outside them
+    int64_t base = A.off[s];
+    int64_t end = base + A.cnt[(size_t)s * A.cstride];
+    base = base < 0 ? 0 : (base > A.len ? A.len : base);
+    end = end < base ? base : (end > A.len ? A.len : end);
+
+    Run own;                              // run `lane` of the shower
+    run_clear(own);
+    int R = 0, prev = -1;                 // runs so far, the layer of the last hit
+    while (base < end && R <= WAVE) {
+        const int raw = (int)(end - base < SHW_TILE ? end - base : SHW_TILE);
+        const int rb = R > 0 ? R - 1 : 0; // the run that may go on in this tile
+        const bool goes_on = R > 0;
+        int m = 0;                        // hits in the tile
+        if (lane < 3) T.hit[lane][SHW_TILE] = 0.0f;
+        for (int b = 0; b < raw; b += SHW_STEP) {
+            const int here = raw - b < SHW_STEP ? raw - b : SHW_STEP;
+            Four h = read_four(A, base + b, here, lane);
+            uint64_t in[4], out = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                in[u] = lanes_with(here, u);
+                out |= __ballot(h.l[u] < 0) & in[u];
+            }
+            int p[4], at = m + 4 * lane;  // the layer before each hit, the first hit's place
+            uint64_t st[4];               // lanes whose hit u starts a run
+            if (!out && !(m & 3)) {       // every hit is taken
+                p[0] = __builtin_amdgcn_update_dpp(prev, h.l[3], 0x138, 0xf, 0xf, false);   // lane - 1's last
+#pragma unroll
+                for (int u = 1; u < 4; ++u) p[u] = h.l[u - 1];
+                *(f32x4 *)&T.hit[0][at] = h.x;
+                *(f32x4 *)&T.hit[1][at] = h.y;
+                *(f32x4 *)&T.hit[2][at] = h.e;
+                m += here;
+                // (a partial step is the segment's last)
+                prev = __builtin_amdgcn_readlane(h.l[3], WAVE - 1);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) st[u] = __ballot(h.l[u] != p[u]) & in[u];
+            } else {
+                int last = -1;            // the lane's last layer
+                at = m;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    h.l[u] = 4 * lane + u < here ? h.l[u] : -1;
+                    last = h.l[u] >= 0 ? h.l[u] : last;
+                    const uint64_t vm = __ballot(h.l[u] >= 0);
+                    at += lanes_below(vm);
+                    m += (int)__builtin_popcountll(vm);
+                }
+                const uint64_t hm = __ballot(last >= 0);
+                const uint64_t below = hm & ((1ull << lane) - 1ull);
+                const int before = __shfl(last, below ? 63 - __builtin_clzll(below) : lane);
+                int q = below ? before : prev, a = at;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    p[u] = q;
+                    if (h.l[u] >= 0) {
+                        q = h.l[u];
+                        T.hit[0][a] = h.x[u];
+                        T.hit[1][a] = h.y[u];
+                        T.hit[2][a] = h.e[u];
+                        ++a;
+                    }
+                    st[u] = __ballot(h.l[u] >= 0 && h.l[u] != p[u]);
+                }
+                if (hm) prev = __builtin_amdgcn_readlane(last, 63 - __builtin_clzll(hm));
+            }
+            if (st[0] | st[1] | st[2] | st[3]) {
+                int r = R;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    r += lanes_below(st[u]);
+                    R += (int)__builtin_popcountll(st[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool start = (st[u] >> lane) & 1;
+                    if (start && r < WAVE) {
+                        T.pos[r] = at;
+                        T.lay[r] = h.l[u];
+                    }
+                    r += start ? 1 : 0;
+                    at += h.l[u] >= 0 ? 1 : 0;
+                }
+            }
+        }
+        base += raw;
+        if (R > WAVE) break;              // a layer comes twice
+        if (m == 0) continue;
+        wave_sync();
+        // this lane's run in the tile: [p0, p1)
+        const bool here = lane >= rb && lane < R;
+        const int p0 = !here ? 0 : (goes_on && lane == rb) ? 0 : T.pos[lane];
+        const int p1 = !here ? 0 : lane + 1 < R ? T.pos[lane + 1] : m;
+        const int nr = p1 - p0;
+        // fragment length F: the runs' last fragments are half full on average
+        // (try that first); m / (64 - runs) always fits, and so does the
+        // longest run.  nr + F <= 2 SHW_TILE: the quotients are exact.
+        const int runs = R - rb, longest = wave_max(nr);
+        const int free_ = WAVE - (runs >> 1);
+        int F = min(longest, 1 + (int)((float)(m - 1) * __builtin_amdgcn_rcpf((float)free_)));
+        int cnt = (int)(((float)(nr + F) - 0.5f) * __builtin_amdgcn_rcpf((float)F));
+        int off = scan_sum(cnt);
+        int total = __builtin_amdgcn_readlane(off, WAVE - 1);
+        if (total > WAVE) {
+            F = runs < WAVE ? min(longest, 1 + (int)((float)m * __builtin_amdgcn_rcpf((float)(WAVE - runs))))
+                            : longest;
+            cnt = (int)(((float)(nr + F) - 0.5f) * __builtin_amdgcn_rcpf((float)F));
+            off = scan_sum(cnt);
+            total = __builtin_amdgcn_readlane(off, WAVE - 1);
+        }
+        off -= cnt;
+        // lane j takes fragment j: of the run whose first fragment is the last at or before j
+        T.flag[lane] = -1;
+        wave_sync();
+        if (cnt > 0) T.flag[off] = lane;
+        wave_sync();
+        const int fl = T.flag[lane];
+        const uint64_t firsts = __ballot(fl >= 0);
+        const int f0 = 63 - __builtin_clzll(firsts & ((2ull << lane) - 1ull));   // (fragment 0 is a first one)
+        const int run = __shfl(fl, f0);
+        const int a0 = __shfl(p0, run) + (lane - f0) * F;
+        const int left = __shfl(p1, run) - a0;
+        const int len = lane < total ? min(F, left) : 0;
+        Run acc;
+        run_clear(acc);
+        for (int k = 0; k < F; ++k) {
+            const int i = k < len ? a0 + k : SHW_TILE;
+            run_add(acc, T.hit[0][i], T.hit[1][i], T.hit[2][i], k < len);
+        }
+        wave_sync();
+        T.f.d[0][lane] = acc.sx;
+        T.f.d[1][lane] = acc.sxx;
+        T.f.d[2][lane] = acc.sy;
+        T.f.d[3][lane] = acc.syy;
+        T.f.d[4][lane] = acc.sr;
+        T.f.d[5][lane] = acc.se;
+        T.f.d[6][lane] = acc.see;
+        T.f.d[7][lane] = acc.sex;
+        T.f.d[8][lane] = acc.sexx;
+        T.f.d[9][lane] = acc.sey;
+        T.f.d[10][lane] = acc.seyy;
+        T.f.d[11][lane] = acc.ser;
+        // the two largest energies of the run's fragments up to this one, in
+        // the row of sixteen
+        seg_top<1>(acc.e1, acc.e2, run);
+        seg_top<2>(acc.e1, acc.e2, run);
+        seg_top<4>(acc.e1, acc.e2, run);
+        seg_top<8>(acc.e1, acc.e2, run);
+        T.f.top[lane] = f32x2{acc.e1, acc.e2};
+        wave_sync();
+        // running sums over sixteen fragments, starting anew at each run
+        if ((lane & 15) < SHW_SUMS) {
+            f64x2 *row = (f64x2 *)&T.f.d[lane & 15][lane & 48];
+            const int bits = (int)(uint32_t)(firsts >> (lane & 48));
+            double sum = 0.0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                f64x2 w = row[k];
+                sum = ((bits >> (2 * k)) & 1) ? w.x : sum + w.x;
+                w.x = sum;
+                sum = ((bits >> (2 * k + 1)) & 1) ? w.y : sum + w.y;
+                w.y = sum;
+                row[k] = w;
+            }
+        }
+        wave_sync();
+        // the run's partial sums, one per sixteen fragments it has a part in
+        const int lastf = off + cnt - 1;
+        int f = cnt > 0 ? min(off | 15, lastf) : WAVE;
+        while (__ballot(f <= lastf)) {
+            if (f <= lastf) {
+                own.sx += T.f.d[0][f];
+                own.sxx += T.f.d[1][f];
+                own.sy += T.f.d[2][f];
+                own.syy += T.f.d[3][f];
+                own.sr += T.f.d[4][f];
+                own.se += T.f.d[5][f];
+                own.see += T.f.d[6][f];
+                own.sex += T.f.d[7][f];
+                own.sexx += T.f.d[8][f];
+                own.sey += T.f.d[9][f];
+                own.seyy += T.f.d[10][f];
+                own.ser += T.f.d[11][f];
+                add_top(own.e1, own.e2, T.f.top[f].x, T.f.top[f].y);
+                f = f == lastf ? WAVE : min(f + 16, lastf);
+            }
+        }
+        own.n += nr;
+        wave_sync();
+    }
+
+    // layers seen; a layer seen twice or out of range spoils the shower
+    const bool mine = lane < R && R <= WAVE;
+    const int l = mine ? T.lay[lane] : -1;
+    uint64_t seen = 0;
+    for (int r = 0; r < R && r < WAVE; ++r) {
+        const int lr = __builtin_amdgcn_readlane(l, r);
+        seen |= lr >= 0 && lr < 64 ? 1ull << lr : 0ull;
+    }
+    const bool bad = R > WAVE || __ballot(mine && l >= L) || (int)__builtin_popcountll(seen) != R;
+    float *out = A.lv + (size_t)s * L * LV, *sv = A.sv + (size_t)s * SV;
+    if (bad) {
+        for (int f = lane; f < L * LV; f += WAVE) out[f] = nan;
+        if (lane < SV) sv[lane] = nan;
+        if (lane == 0) atomicAdd(A.work, 1);
+        return;
+    }
+    const double se = mine ? own.se : 0.0;
+    const double etot = wave_sum(se);
+    const double ld = wave_sum((double)l * se), ld2 = wave_sum((double)l * (double)l * se);
+    const int depth = wave_max(mine && own.se > 0.0 ? l + 1 : 0) - 1;
+    const double it = etot > 0.0 ? recip(etot) : 0.0;
+    if (mine) {
+        write_layer(out + (size_t)l * LV, own);
+        out[(size_t)l * LV + SUPA_LV_FRACTION] = etot > 0.0 ? (float)((double)(float)own.se * it) : nan;
+    }
+    if (lane < L && !((seen >> lane) & 1)) {
+        write_empty_layer(out + (size_t)lane * LV);
+        out[(size_t)lane * LV + SUPA_LV_FRACTION] = etot > 0.0 ? 0.0f : nan;
+    }
+    if (lane == 0) {
+        const double sd = ld * it;
+        sv[SUPA_SV_E_TOT] = (float)etot;
+        sv[SUPA_SV_DEPTH] = (float)depth;
+        sv[SUPA_SV_L_D] = (float)ld;
+        sv[SUPA_SV_S_D] = etot > 0.0 ? (float)sd : nan;
+        sv[SUPA_SV_S_D_WIDTH] = etot > 0.0 ? dev_of(sd, ld2 * it) : nan;
+    }
+}
+
+__global__ void __launch_bounds__(WAVE) shapes_wave_kernel(ShapeArgs A) {
+    __shared__ __attribute__((aligned(16))) WaveTile T;
+    if (!A.work[2]) return;               // a lane each
+    const int lane = threadIdx.x;
+    for (int64_t s = blockIdx.x; s < A.n; s += gridDim.x) {
+        wave_shower(A, T, s, lane);
+        wave_sync();                      // (the tile is used again)
+    }
 }
 
 __global__ void radius_kernel(int64_t n, const float *x, const float *y, float *r) {
@@ -858,25 +1282,30 @@ extern "C" supa_status supa_shower_shapes(void *stream, int64_t n, int32_t n_lay
         return bad_arg("hit arrays must be 16-byte aligned");
     if (n > 0 && ((uintptr_t)layer_vars & 7)) return bad_arg("layer_vars must be 8-byte aligned");
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(shapes_clear, dim3(1), dim3(1024), 0, s, work);
+    const int64_t few = (int64_t)cu_count() * WAVE_CALLS;
+    hipLaunchKernelGGL(shapes_clear, dim3(1), dim3(1024), 0, s, work, n, hit_offsets, hit_counts, counts_stride,
+                       n <= few ? 1 : 0);
     if (n == 0) return dev_err(hipGetLastError(), "shapes_clear");
+    int32_t *order = work + WORK_HEAD;
+    const int32_t *by_wave = work + 2;
+    ShapeArgs A{n, n_layers, hit_offsets, hit_counts, counts_stride, hit_len, hit_x, hit_y, hit_e,
+                hit_layer, layer_vars, shower_vars, work, order};
+    hipLaunchKernelGGL(shapes_wave_kernel, dim3((unsigned)(n < 2 * few ? n : 2 * few)), dim3(WAVE), 0, s, A);
+    if (n <= few) return dev_err(hipGetLastError(), "shapes_wave_kernel");
     const int64_t waves = (n + WAVE - 1) / WAVE;
     const int64_t cap = (int64_t)cu_count() * 16;
     const int grid = (int)(waves < cap ? waves : cap);
-    int32_t *order = work + WORK_HEAD;
     if (waves <= cap) {  // every shower in flight at once (one per lane): one order
         uint32_t *gsize = (uint32_t *)work + 4, *gcur = gsize + ORDER_BUCKETS;
         const int blocks = (int)((n + ORDER_CHUNK - 1) / ORDER_CHUNK);
         hipLaunchKernelGGL(shapes_order_sizes, dim3(blocks), dim3(ORDER_THREADS), 0, s, n, hit_counts,
-                           counts_stride, gsize);
+                           counts_stride, by_wave, gsize);
         hipLaunchKernelGGL(shapes_order_place, dim3(blocks), dim3(ORDER_THREADS), 0, s, n, hit_counts,
-                           counts_stride, gsize, gcur, order);
+                           counts_stride, by_wave, gsize, gcur, order);
     } else {
         hipLaunchKernelGGL(shapes_order, dim3((int)((n + ORDER_WIN - 1) / ORDER_WIN)), dim3(ORDER_THREADS), 0,
-                           s, n, (int64_t)ORDER_WIN, hit_counts, counts_stride, order);
+                           s, n, (int64_t)ORDER_WIN, hit_counts, counts_stride, by_wave, order);
     }
-    ShapeArgs A{n, n_layers, hit_offsets, hit_counts, counts_stride, hit_len, hit_x, hit_y, hit_e,
-                hit_layer, layer_vars, shower_vars, work, order};
     hipLaunchKernelGGL(shapes_kernel, dim3(grid), dim3(WAVE), (size_t)n_layers * WAVE * sizeof(float),
                        s, A);
     return dev_err(hipGetLastError(), "shapes_kernel");
