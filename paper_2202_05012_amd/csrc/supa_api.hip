@@ -19,7 +19,7 @@
 #include "supa_device.hpp"
 
 namespace supa {
-hipError_t launch_zero_counters(unsigned long long *ctr, hipStream_t s);
+hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold, hipStream_t s);
 hipError_t launch_note_chunks(const unsigned long long *ctr, unsigned long long *sub, hipStream_t s);
 hipError_t launch_propagate(const Params &P, bool literal, bool rings, int blocks, hipStream_t s);
 hipError_t launch_philox(const uint32_t *ctr, int64_t n, uint32_t k0, uint32_t k1, uint32_t *out,
@@ -873,13 +873,16 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
 // ev_prop[j], ev_post[j], ev_place[j]: the events of sub-batch j (the
 // context's, or a call's own in supa_simulate_batches).  join: the main
 // stream waits for the second stream at the end.
+// h_cold: the blocks, to be written to d_cold (null: they are there already).
+// h_ctr: where the last scan leaves the counters for the host, or null.
 static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, const Plan &L,
-                           supa::Cold *d_cold, hipStream_t s_main, hipStream_t s_aux, bool timed,
+                           supa::Cold *d_cold, const supa::Cold *h_cold, unsigned long long *h_ctr,
+                           hipStream_t s_main, hipStream_t s_aux, bool timed,
                            hipEvent_t (*ev_prop)[2], hipEvent_t (*ev_post)[2], hipEvent_t *ev_place,
                            bool join = true) {
     auto sub_ctr = [&](int j) { return L.ctr + supa::CTR_BLOCK * (1 + j); };
     const supa::Params &P = L.P;
-    HIP_TRY(c, supa::launch_zero_counters(L.ctr, s_main));
+    HIP_TRY(c, supa::launch_begin(L.ctr, d_cold, h_cold, h_cold ? L.nsub : 0, s_main));
     for (int j = 0; j < L.nsub; ++j) {
         const int64_t o = L.off(j), nj = L.off(j + 1) - o;
         supa::Params Pj = P;
@@ -903,7 +906,8 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
             Pp.pool_cap = P.pool_cap;
             HIP_TRY(c, supa::launch_propagate(Pp, false, false, (int)L.waves, s_main));
         }
-        if (L.tree) HIP_TRY(c, supa::launch_note_chunks(L.ctr, sub_ctr(j), s_main));
+        // (a single propagation's chunks: noted by the scan)
+        if (L.tree && L.nsub > 1) HIP_TRY(c, supa::launch_note_chunks(L.ctr, sub_ctr(j), s_main));
         // the second stream waits on this event (none inside a capture, where
         // both are one stream)
         const bool two = s_aux != s_main;
@@ -918,6 +922,9 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
         SP.partial = L.d_part;
         SP.sub = sub_ctr(j);
         SP.prev = j > 0 ? sub_ctr(j - 1) : nullptr;
+        SP.ctr = L.ctr;
+        SP.host = j == L.nsub - 1 ? h_ctr : nullptr;
+        SP.note_chunks = L.tree && L.nsub == 1;
 
         supa::PlaceParams H{};
         H.n = (int32_t)nj;
@@ -973,7 +980,7 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
         HIP_TRY(c, supa::launch_scan(SP, s_aux));
         if (timed) HIP_TRY(c, hipEventRecord(ev_post[j][0], s_aux));
         if (L.recs) HIP_TRY(c, supa::launch_place(H, c->n_cu, s_aux));
-        if (timed) HIP_TRY(c, hipEventRecord(ev_place[j], s_aux));
+        if (timed && L.recs && L.tree) HIP_TRY(c, hipEventRecord(ev_place[j], s_aux));
         if (L.tree) HIP_TRY(c, supa::launch_scatter_nodes(Q, (int32_t)nj, c->n_cu, s_aux));
         if (timed || two) HIP_TRY(c, hipEventRecord(ev_post[j][1], s_aux));
     }
@@ -1048,23 +1055,30 @@ static void size_logs(supa_ctx *c, const supa_batch *b, const supa_output *out) 
 // Runs a prepared call once: launches it, reads back its counters (one
 // synchronisation) and records the kernel times.
 static supa_status run_once(supa_ctx *c, const supa_batch *b, supa_output *out, const Plan &L) {
-    HIP_TRY(c, hipMemcpyAsync(c->d_cold, c->h_cold, L.nsub * sizeof(supa::Cold), hipMemcpyHostToDevice,
-                              c->stream));
-    HIP_TRY(c, hipEventRecord(c->ev_begin, c->stream));
-    supa_status st = enqueue(c, b, out, L, c->d_cold, c->stream, c->aux, true, c->ev_prop, c->ev_post, c->ev_place);
+    // One sub-batch: nothing would overlap on a second stream, so all of it is
+    // one chain on the caller's.
+    const bool one = L.nsub == 1;
+    const bool ordered = L.d_order != nullptr;
+    if (!one || ordered) HIP_TRY(c, hipEventRecord(c->ev_begin, c->stream));
+    supa_status st = enqueue(c, b, out, L, c->d_cold, c->h_cold, L.post ? c->h_ctr : nullptr, c->stream,
+                             one ? c->stream : c->aux, true, c->ev_prop, c->ev_post, c->ev_place);
     if (st != SUPA_OK) return st;
-    HIP_TRY(c, hipMemcpyAsync(c->h_ctr, L.ctr, supa::CTR_WORDS * sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipEventRecord(c->ev_end, c->stream));
+    if (!L.post)
+        HIP_TRY(c, hipMemcpyAsync(c->h_ctr, L.ctr, supa::CTR_WORDS * sizeof(unsigned long long),
+                                  hipMemcpyDeviceToHost, c->stream));
+    if (!one) HIP_TRY(c, hipEventRecord(c->ev_end, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     float t_prop = 0, t_post = 0, t_all = 0, t_place = 0, t_scatter = 0, t = 0;
     for (int j = 0; j < L.nsub; ++j) {
         if (hipEventElapsedTime(&t, c->ev_prop[j][0], c->ev_prop[j][1]) == hipSuccess) t_prop += t;
         if (L.post && hipEventElapsedTime(&t, c->ev_post[j][0], c->ev_post[j][1]) == hipSuccess) t_post += t;
-        if (L.recs && hipEventElapsedTime(&t, c->ev_post[j][0], c->ev_place[j]) == hipSuccess) t_place += t;
-        if (L.tree && hipEventElapsedTime(&t, c->ev_place[j], c->ev_post[j][1]) == hipSuccess) t_scatter += t;
+        if (L.recs && hipEventElapsedTime(&t, c->ev_post[j][0], L.tree ? c->ev_place[j] : c->ev_post[j][1]) == hipSuccess)
+            t_place += t;
+        if (L.tree && hipEventElapsedTime(&t, L.recs ? c->ev_place[j] : c->ev_post[j][0], c->ev_post[j][1]) == hipSuccess)
+            t_scatter += t;
     }
-    (void)hipEventElapsedTime(&t_all, c->ev_begin, c->ev_end);
+    (void)hipEventElapsedTime(&t_all, !one || ordered ? c->ev_begin : c->ev_prop[0][0],
+                              !one ? c->ev_end : L.post ? c->ev_post[0][1] : c->ev_prop[0][1]);
     (void)hipGetLastError();
     c->timing[0] = t_prop;
     c->timing[1] = t_post;
@@ -1196,7 +1210,7 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
             if (j >= 2) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_set_free[q], 0));
             hipEvent_t *e = &c->call_ev[(size_t)j * 5];
             hipEvent_t ev_prop[1][2] = {{e[0], e[1]}}, ev_post[1][2] = {{e[2], e[4]}}, ev_place[1] = {e[3]};
-            st = enqueue(c, &b[j], &out[j], plans[j], d_calls + j, c->stream, c->aux, true, ev_prop, ev_post,
+            st = enqueue(c, &b[j], &out[j], plans[j], d_calls + j, nullptr, nullptr, c->stream, c->aux, true, ev_prop, ev_post,
                          ev_place, false);
             if (st != SUPA_OK) return st;
             // counters-only calls have no second-stream part: order after the propagation
@@ -1216,8 +1230,8 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
             const hipEvent_t *e = &c->call_ev[(size_t)j * 5];
             if (hipEventElapsedTime(&t, e[0], e[1]) == hipSuccess) t_prop += t;
             if (plans[j].post && hipEventElapsedTime(&t, e[2], e[4]) == hipSuccess) t_post += t;
-            if (plans[j].recs && hipEventElapsedTime(&t, e[2], e[3]) == hipSuccess) t_place += t;
-            if (plans[j].tree && hipEventElapsedTime(&t, e[3], e[4]) == hipSuccess) t_scatter += t;
+            if (plans[j].recs && hipEventElapsedTime(&t, e[2], e[plans[j].tree ? 3 : 4]) == hipSuccess) t_place += t;
+            if (plans[j].tree && hipEventElapsedTime(&t, e[plans[j].recs ? 3 : 2], e[4]) == hipSuccess) t_scatter += t;
         }
         (void)hipEventElapsedTime(&t_all, c->ev_begin, c->ev_end);
         (void)hipGetLastError();
@@ -1296,7 +1310,7 @@ extern "C" supa_status supa_graph_create(supa_ctx *c, const supa_batch *b, uint6
     if (e == hipSuccess) e = hipMemcpy(g->d_cold, c->h_cold, sizeof(supa::Cold), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamBeginCapture(c->aux, hipStreamCaptureModeRelaxed);
     if (e == hipSuccess) {
-        st = enqueue(c, b, out, g->plan, g->d_cold, c->aux, c->aux, false, c->ev_prop, c->ev_post, c->ev_place);
+        st = enqueue(c, b, out, g->plan, g->d_cold, nullptr, nullptr, c->aux, c->aux, false, c->ev_prop, c->ev_post, c->ev_place);
         const hipError_t e2 = hipStreamEndCapture(c->aux, &graph);
         if (st == SUPA_OK && e2 != hipSuccess) e = e2;
     }

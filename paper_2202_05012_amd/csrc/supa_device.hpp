@@ -164,6 +164,9 @@ struct ScanParams {
     int64_t *partial;           // [2][ceil(n / SCAN_TILE)] tile sums, then tile offsets
     unsigned long long *sub;    // SUB_HITS / SUB_NODES receive the running totals
     const unsigned long long *prev;   // the previous sub-batch's counters, or null
+    const unsigned long long *ctr;    // the call's counters
+    unsigned long long *host;         // pinned host copy of the counters, written after the scan, or null
+    bool note_chunks;                 // SUB_NCHUNK_END of sub is taken from the counters
 };
 constexpr int SCAN_THREADS = 256, SCAN_ITEMS = 16, SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 
@@ -224,6 +227,9 @@ enum {
     SUB_NCHUNK_END = 3   // node-log chunks claimed when the sub-batch's propagation ended
 };
 constexpr int MAX_SUB = 8;
+struct ColdBlocks {
+    Cold c[MAX_SUB];
+};
 // Subtree work items: after the sub-batch blocks, the shares handed out,
 // then per launch phase the items it exported and the items claimed from it.
 constexpr int MAX_PHASES = 4;

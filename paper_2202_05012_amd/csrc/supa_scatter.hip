@@ -1,9 +1,10 @@
 // supa_scatter.hip -- segment offsets, and tree nodes to their places.
 //
 //   scan     hit and node segment offsets = exclusive prefix sums of the
-//            showers' counts in batch order (three small kernels: tile sums,
-//            one-block scan of the tile sums, per-tile scan), so the output
-//            layout is the same on every run;
+//            showers' counts in batch order (one block up to SCAN_ONE
+//            showers, else three small kernels: tile sums, one-block scan of
+//            the tile sums, per-tile scan), so the output layout is the same
+//            on every run;
 //   scatter  every node record of the log (chunks filled in whatever order
 //            the waves produced them) goes to its shower's segment start +
 //            its index within the shower.  Pure data movement.
@@ -14,6 +15,8 @@
 #include "supa_device.hpp"
 
 namespace supa {
+
+constexpr int SCAN_ONE = 16 * 1024;     // showers that one block scans
 
 __device__ __forceinline__ long long block_sum_ll(long long v, long long *sh) {
 #pragma unroll
@@ -70,6 +73,75 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_tiles(ScanParams S) {
     }
 }
 
+// After the scan (one block): the chunks claimed so far, and the call's
+// counters to the host.  Nothing later in the call writes them, so the host
+// need not copy them back: a copy of 5 KB between two kernels and the
+// synchronisation took 10 to 15 us.
+__device__ __forceinline__ void publish_counters(const ScanParams &S) {
+    if (S.note_chunks && threadIdx.x == 0) S.sub[SUB_NCHUNK_END] = S.ctr[CTR_NCHUNK];
+    if (!S.host) return;
+    __threadfence();
+    __syncthreads();
+    for (int q = (int)threadIdx.x; q < CTR_WORDS; q += (int)blockDim.x)
+        __hip_atomic_store(S.host + q, __hip_atomic_load(S.ctr + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+}
+
+// Up to SCAN_ONE showers: all of it by one block (a call of 1,000 showers is a
+// chain of short launches: 4 us each and as much between them).  Wave w scans
+// 64 * ceil(n / 1024) consecutive showers, their counts held in registers.
+__global__ void __launch_bounds__(1024) scan_one(ScanParams S) {
+    __shared__ long long sh[2][16];
+    const int lane = (int)(threadIdx.x & 63), w = (int)threadIdx.x >> 6;
+    const int per = (S.n + 1023) / 1024;
+    const int base = w * per * 64 + lane;
+    int32_t v[2][SCAN_ONE / 1024];
+    long long sum[2] = {0, 0};
+#pragma unroll
+    for (int q = 0; q < SCAN_ONE / 1024; ++q) {
+        const int64_t i = base + q * 64;
+        const bool in = q < per && i < S.n;
+        v[0][q] = in ? S.counts[6 * i + 1] : 0;
+        v[1][q] = in ? S.counts[6 * i] : 0;
+        sum[0] += v[0][q];
+        sum[1] += v[1][q];
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum[a] += __shfl_xor(sum[a], off, 64);
+        if (lane == 0) sh[a][w] = sum[a];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        int64_t *out = a == 0 ? S.hoff : S.noff;
+        // sub-batches after the first continue the previous running total
+        long long o = S.prev ? (long long)S.prev[a == 0 ? SUB_HITS : SUB_NODES] : 0, all = o;
+        for (int q = 0; q < 16; ++q) {
+            if (q < w) o += sh[a][q];
+            all += sh[a][q];
+        }
+        if (threadIdx.x == 0) S.sub[a == 0 ? SUB_HITS : SUB_NODES] = (unsigned long long)all;
+        if (!out) continue;
+#pragma unroll
+        for (int q = 0; q < SCAN_ONE / 1024; ++q) {
+            if (q >= per) break;
+            long long incl = v[a][q];
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const long long t = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += t;
+            }
+            const int64_t i = base + q * 64;
+            if (i < S.n) out[i] = o + incl - v[a][q];
+            o += __shfl(incl, 63, 64);
+        }
+    }
+    publish_counters(S);
+}
+
 // one block: tile sums -> tile offsets (in place), totals into the counters
 __global__ void __launch_bounds__(1024) scan_top(ScanParams S) {
     __shared__ long long sh[16];
@@ -87,6 +159,7 @@ __global__ void __launch_bounds__(1024) scan_top(ScanParams S) {
         }
         if (threadIdx.x == 0) S.sub[a == 0 ? SUB_HITS : SUB_NODES] = (unsigned long long)carry;
     }
+    publish_counters(S);
 }
 
 // per tile: offsets of its showers (SCAN_ITEMS consecutive showers per thread)
@@ -185,6 +258,10 @@ int64_t scan_partial_words(int64_t n) { return 2 * ((n + SCAN_TILE - 1) / SCAN_T
 
 hipError_t launch_scan(const ScanParams &S, hipStream_t s) {
     if (S.n <= 0) return hipSuccess;
+    if (S.n <= SCAN_ONE) {
+        hipLaunchKernelGGL(scan_one, dim3(1), dim3(1024), 0, s, S);
+        return hipGetLastError();
+    }
     const int nt = (int)((S.n + SCAN_TILE - 1) / SCAN_TILE);
     hipLaunchKernelGGL(scan_tiles, dim3(nt), dim3(SCAN_THREADS), 0, s, S);
     hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, S);
