@@ -403,8 +403,9 @@ supa_status supa_graph_check(supa_graph *graph, void *hip_stream, int64_t *total
 supa_status supa_graph_destroy(supa_graph *graph);
 
 /*
- * Device time of the last supa_simulate, in milliseconds, measured with HIP
- * events: [0] propagation kernels (summed over sub-batches), [1] placement
+ * Device time of the last supa_simulate, in milliseconds (from the device's
+ * wall clock, stamped by the kernels, or from HIP events where parts overlap):
+ * [0] propagation kernels (summed over sub-batches), [1] placement
  * of hits, images and nodes (summed; with sub-batches they overlap [0]),
  * [2] whole call (including work ordering and segment offsets).  Host
  * pointer to 3 floats.

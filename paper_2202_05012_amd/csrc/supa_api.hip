@@ -19,7 +19,8 @@
 #include "supa_device.hpp"
 
 namespace supa {
-hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold, hipStream_t s);
+hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold,
+                        unsigned long long *clk, hipStream_t s);
 hipError_t launch_note_chunks(const unsigned long long *ctr, unsigned long long *sub, hipStream_t s);
 hipError_t launch_propagate(const Params &P, bool literal, bool rings, int blocks, hipStream_t s);
 hipError_t launch_philox(const uint32_t *ctr, int64_t n, uint32_t k0, uint32_t k1, uint32_t *out,
@@ -122,6 +123,7 @@ struct supa_ctx {
     uint64_t *d_c1 = nullptr, *d_c2 = nullptr;
     unsigned long long *d_ctr = nullptr;
     unsigned long long *h_ctr = nullptr;   // pinned
+    unsigned long long *d_clk = nullptr;   // time stamps of a call's kernels
     supa::Cold *d_cold = nullptr;          // per-sub-batch inputs/outputs blocks (device)
     supa::Cold *h_cold = nullptr;          // their pinned host staging copy
     // launch settings and scratch
@@ -174,7 +176,8 @@ struct supa_ctx {
     hipEvent_t ev_place[supa::MAX_SUB] = {};      // end of the hit / image placement (aux)
     // propagation, placement + node scatter, whole call, placement alone,
     // node scatter alone (ms, summed over sub-batches)
-    float timing[5] = {0, 0, 0, 0, 0};
+    mutable float timing[5] = {0, 0, 0, 0, 0};
+    mutable bool stamped = false;        // timing is still to be taken from d_clk
     std::string err;
     bool broken = false;
 };
@@ -375,6 +378,8 @@ extern "C" supa_status supa_init_geometry(const supa_geometry *g, int device, vo
                         hipMemcpyHostToDevice) == hipSuccess &&
               hipMalloc(&c->d_c2, THR_ENTRIES * sizeof(uint64_t)) == hipSuccess &&
               hipMalloc(&c->d_ctr, 2 * supa::CTR_WORDS * sizeof(unsigned long long)) == hipSuccess &&
+              hipMalloc(&c->d_clk, supa::CLK_WORDS * sizeof(unsigned long long)) == hipSuccess &&
+              hipMemset(c->d_clk, 0, supa::CLK_WORDS * sizeof(unsigned long long)) == hipSuccess &&
               hipHostMalloc(&c->h_ctr, supa::CTR_WORDS * sizeof(unsigned long long), 0) == hipSuccess &&
               hipMalloc(&c->d_cold, supa::MAX_SUB * sizeof(supa::Cold)) == hipSuccess &&
               hipMalloc(&c->d_wclk, (size_t)2 * 32 * c->n_cu * sizeof(unsigned long long)) == hipSuccess &&
@@ -423,6 +428,7 @@ extern "C" supa_status supa_destroy(supa_ctx *c) {
     if (c->d_c2) (void)hipFree(c->d_c2);
     if (c->d_ctr) (void)hipFree(c->d_ctr);
     if (c->h_ctr) (void)hipHostFree(c->h_ctr);
+    if (c->d_clk) (void)hipFree(c->d_clk);
     if (c->d_cold) (void)hipFree(c->d_cold);
     if (c->d_wclk) (void)hipFree(c->d_wclk);
     if (c->h_cold) (void)hipHostFree(c->h_cold);
@@ -488,9 +494,40 @@ extern "C" supa_status supa_last_subtrees(const supa_ctx *c, int64_t *counts5) {
     return SUPA_OK;
 }
 
+// Times of a call whose kernels stamped the clock (after its end).  Stamps
+// older than the call are of earlier ones with more workgroups.
+static void resolve_timing(const supa_ctx *c) {
+    if (!c->stamped) return;
+    c->stamped = false;
+    int rate_khz = 0;
+    unsigned long long h[supa::CLK_WORDS];
+    if (hipSetDevice(c->device) != hipSuccess ||
+        hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, c->device) != hipSuccess || rate_khz <= 0 ||
+        hipMemcpy(h, c->d_clk, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess) {
+        (void)hipGetLastError();
+        std::fill(c->timing, c->timing + 5, 0.0f);
+        return;
+    }
+    const unsigned long long begin = h[supa::CLK_BEGIN], scan = h[supa::CLK_SCAN];
+    unsigned long long first[2] = {~0ull, ~0ull}, last[2] = {0, 0};
+    for (int a = 0; a < 2; ++a)
+        for (int q = 0; q < supa::CLK_SLOTS; ++q) {
+            const unsigned long long *t = h + (a == 0 ? supa::CLK_PLACE : supa::CLK_SCATTER) + q;
+            if (t[0] >= scan) first[a] = std::min(first[a], t[0]);
+            if (t[supa::CLK_SLOTS] >= scan) last[a] = std::max(last[a], t[supa::CLK_SLOTS]);
+        }
+    auto ms = [&](unsigned long long a, unsigned long long b) { return b > a ? (float)((double)(b - a) / rate_khz) : 0.0f; };
+    c->timing[0] = ms(begin, scan);
+    c->timing[1] = ms(std::min(first[0], first[1]), std::max(last[0], last[1]));
+    c->timing[2] = ms(begin, std::max({scan, last[0], last[1]}));
+    c->timing[3] = ms(first[0], last[0]);
+    c->timing[4] = ms(first[1], last[1]);
+}
+
 extern "C" supa_status supa_last_timing(const supa_ctx *c, float *ms3) {
     if (!c) return SUPA_ERR_STATE;
     if (!ms3) return SUPA_ERR_INVALID_ARG;
+    resolve_timing(c);
     std::memcpy(ms3, c->timing, 3 * sizeof(float));
     return SUPA_OK;
 }
@@ -499,6 +536,7 @@ extern "C" supa_status supa_last_kernel_times(const supa_ctx *c, float *ms, int3
     if (!c) return SUPA_ERR_STATE;
     if (!ms || count < 0) return SUPA_ERR_INVALID_ARG;
     const int m = std::min<int>(count, 5);
+    resolve_timing(c);
     std::memcpy(ms, c->timing, (size_t)m * sizeof(float));
     for (int q = m; q < count; ++q) ms[q] = 0.0f;
     return SUPA_OK;
@@ -875,14 +913,16 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
 // stream waits for the second stream at the end.
 // h_cold: the blocks, to be written to d_cold (null: they are there already).
 // h_ctr: where the last scan leaves the counters for the host, or null.
+// clk: the kernels' time stamps, or null.
 static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, const Plan &L,
                            supa::Cold *d_cold, const supa::Cold *h_cold, unsigned long long *h_ctr,
+                           unsigned long long *clk,
                            hipStream_t s_main, hipStream_t s_aux, bool timed,
                            hipEvent_t (*ev_prop)[2], hipEvent_t (*ev_post)[2], hipEvent_t *ev_place,
                            bool join = true) {
     auto sub_ctr = [&](int j) { return L.ctr + supa::CTR_BLOCK * (1 + j); };
     const supa::Params &P = L.P;
-    HIP_TRY(c, supa::launch_begin(L.ctr, d_cold, h_cold, h_cold ? L.nsub : 0, s_main));
+    HIP_TRY(c, supa::launch_begin(L.ctr, d_cold, h_cold, h_cold ? L.nsub : 0, clk, s_main));
     for (int j = 0; j < L.nsub; ++j) {
         const int64_t o = L.off(j), nj = L.off(j + 1) - o;
         supa::Params Pj = P;
@@ -925,6 +965,7 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
         SP.ctr = L.ctr;
         SP.host = j == L.nsub - 1 ? h_ctr : nullptr;
         SP.note_chunks = L.tree && L.nsub == 1;
+        SP.clk = clk;
 
         supa::PlaceParams H{};
         H.n = (int32_t)nj;
@@ -955,6 +996,7 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
         H.images = L.images ? out->images + L.img_words * o : nullptr;
         H.bucket = L.d_bucket;
         H.bucket_cap = L.bucket_cap;
+        H.clk = clk ? clk + supa::CLK_PLACE : nullptr;
 
         supa::ScatterParams Q{};
         Q.z_first = P.z_first;
@@ -975,6 +1017,7 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
         Q.nvz = out->node_vz;
         Q.ne = out->node_e;
         Q.nk = (L.tree && P.keys) ? out->node_key : nullptr;
+        Q.clk = clk ? clk + supa::CLK_SCATTER : nullptr;
 
         if (two) HIP_TRY(c, hipStreamWaitEvent(s_aux, ev_prop[j][1], 0));
         HIP_TRY(c, supa::launch_scan(SP, s_aux));
@@ -1056,18 +1099,23 @@ static void size_logs(supa_ctx *c, const supa_batch *b, const supa_output *out) 
 // synchronisation) and records the kernel times.
 static supa_status run_once(supa_ctx *c, const supa_batch *b, supa_output *out, const Plan &L) {
     // One sub-batch: nothing would overlap on a second stream, so all of it is
-    // one chain on the caller's.
+    // one chain on the caller's, and its kernels take the times (with a work
+    // order, which belongs to no part, the call is long and events do).
     const bool one = L.nsub == 1;
-    const bool ordered = L.d_order != nullptr;
-    if (!one || ordered) HIP_TRY(c, hipEventRecord(c->ev_begin, c->stream));
-    supa_status st = enqueue(c, b, out, L, c->d_cold, c->h_cold, L.post ? c->h_ctr : nullptr, c->stream,
-                             one ? c->stream : c->aux, true, c->ev_prop, c->ev_post, c->ev_place);
+    const bool stamps = one && L.post && !L.d_order;
+    if (!stamps) HIP_TRY(c, hipEventRecord(c->ev_begin, c->stream));
+    supa_status st = enqueue(c, b, out, L, c->d_cold, c->h_cold, L.post ? c->h_ctr : nullptr,
+                             stamps ? c->d_clk : nullptr, c->stream, one ? c->stream : c->aux, !stamps,
+                             c->ev_prop, c->ev_post, c->ev_place);
     if (st != SUPA_OK) return st;
     if (!L.post)
         HIP_TRY(c, hipMemcpyAsync(c->h_ctr, L.ctr, supa::CTR_WORDS * sizeof(unsigned long long),
                                   hipMemcpyDeviceToHost, c->stream));
-    if (!one) HIP_TRY(c, hipEventRecord(c->ev_end, c->stream));
+    if (!stamps) HIP_TRY(c, hipEventRecord(c->ev_end, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->last_sub_batches = L.nsub;
+    c->stamped = stamps;
+    if (stamps) return SUPA_OK;
     float t_prop = 0, t_post = 0, t_all = 0, t_place = 0, t_scatter = 0, t = 0;
     for (int j = 0; j < L.nsub; ++j) {
         if (hipEventElapsedTime(&t, c->ev_prop[j][0], c->ev_prop[j][1]) == hipSuccess) t_prop += t;
@@ -1077,15 +1125,13 @@ static supa_status run_once(supa_ctx *c, const supa_batch *b, supa_output *out, 
         if (L.tree && hipEventElapsedTime(&t, L.recs ? c->ev_place[j] : c->ev_post[j][0], c->ev_post[j][1]) == hipSuccess)
             t_scatter += t;
     }
-    (void)hipEventElapsedTime(&t_all, !one || ordered ? c->ev_begin : c->ev_prop[0][0],
-                              !one ? c->ev_end : L.post ? c->ev_post[0][1] : c->ev_prop[0][1]);
+    (void)hipEventElapsedTime(&t_all, c->ev_begin, c->ev_end);
     (void)hipGetLastError();
     c->timing[0] = t_prop;
     c->timing[1] = t_post;
     c->timing[2] = t_all;
     c->timing[3] = t_place;
     c->timing[4] = t_scatter;
-    c->last_sub_batches = L.nsub;
     return SUPA_OK;
 }
 
@@ -1210,7 +1256,7 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
             if (j >= 2) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_set_free[q], 0));
             hipEvent_t *e = &c->call_ev[(size_t)j * 5];
             hipEvent_t ev_prop[1][2] = {{e[0], e[1]}}, ev_post[1][2] = {{e[2], e[4]}}, ev_place[1] = {e[3]};
-            st = enqueue(c, &b[j], &out[j], plans[j], d_calls + j, nullptr, nullptr, c->stream, c->aux, true, ev_prop, ev_post,
+            st = enqueue(c, &b[j], &out[j], plans[j], d_calls + j, nullptr, nullptr, nullptr, c->stream, c->aux, true, ev_prop, ev_post,
                          ev_place, false);
             if (st != SUPA_OK) return st;
             // counters-only calls have no second-stream part: order after the propagation
@@ -1235,6 +1281,7 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
         }
         (void)hipEventElapsedTime(&t_all, c->ev_begin, c->ev_end);
         (void)hipGetLastError();
+        c->stamped = false;
         c->timing[0] = t_prop;
         c->timing[1] = t_post;
         c->timing[2] = t_all;
@@ -1310,7 +1357,7 @@ extern "C" supa_status supa_graph_create(supa_ctx *c, const supa_batch *b, uint6
     if (e == hipSuccess) e = hipMemcpy(g->d_cold, c->h_cold, sizeof(supa::Cold), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamBeginCapture(c->aux, hipStreamCaptureModeRelaxed);
     if (e == hipSuccess) {
-        st = enqueue(c, b, out, g->plan, g->d_cold, nullptr, nullptr, c->aux, c->aux, false, c->ev_prop, c->ev_post, c->ev_place);
+        st = enqueue(c, b, out, g->plan, g->d_cold, nullptr, nullptr, nullptr, c->aux, c->aux, false, c->ev_prop, c->ev_post, c->ev_place);
         const hipError_t e2 = hipStreamEndCapture(c->aux, &graph);
         if (st == SUPA_OK && e2 != hipSuccess) e = e2;
     }
@@ -1419,6 +1466,7 @@ extern "C" supa_status supa_autotune(supa_ctx *c, const supa_batch *b, uint64_t 
                         c->cost_order = saved[3];
                         return st;
                     }
+                    resolve_timing(c);
                     if (c->timing[2] < bms) {
                         bms = c->timing[2];
                         bw = w;

@@ -167,7 +167,31 @@ struct ScanParams {
     const unsigned long long *ctr;    // the call's counters
     unsigned long long *host;         // pinned host copy of the counters, written after the scan, or null
     bool note_chunks;                 // SUB_NCHUNK_END of sub is taken from the counters
+    unsigned long long *clk;          // CLK_SCAN is stamped here, or null
 };
+
+// Device times of a call that is one chain of kernels: the kernels store the
+// device's wall clock.  (An event between two kernels is
+// a packet of its own, with a cache write-back: about 5 us each, a quarter of
+// a call of 1,000 showers.)  Ends are kept per workgroup modulo CLK_SLOTS, the
+// last one to end last.
+constexpr int CLK_SLOTS = 64;
+enum {
+    CLK_BEGIN = 0,       // counters cleared
+    CLK_SCAN = 1,        // the scan starts: the propagation is done
+    CLK_PLACE = 8,       // placement: starts, then ends
+    CLK_SCATTER = CLK_PLACE + 2 * CLK_SLOTS,
+    CLK_WORDS = CLK_SCATTER + 2 * CLK_SLOTS
+};
+__device__ inline void stamp(unsigned long long *clk, int slot) {
+    clk[slot] = (unsigned long long)wall_clock64();
+}
+__device__ inline void stamp_start(unsigned long long *clk) {
+    if (clk && threadIdx.x == 0 && blockIdx.x < CLK_SLOTS) stamp(clk, (int)blockIdx.x);
+}
+__device__ inline void stamp_end(unsigned long long *clk) {
+    if (clk && threadIdx.x == 0) stamp(clk, CLK_SLOTS + (int)(blockIdx.x % CLK_SLOTS));
+}
 constexpr int SCAN_THREADS = 256, SCAN_ITEMS = 16, SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 
 // Moves node records to their final places (supa_scatter.hip).
@@ -183,6 +207,7 @@ struct ScatterParams {
     int32_t *np, *ng;
     float *nvx, *nvy, *nvz, *ne;
     uint64_t *nk;               // path ids (or null)
+    unsigned long long *clk;    // 2 * CLK_SLOTS stamps, or null
 };
 
 // Per shower: hit records from the log to the output arrays (grouped by
@@ -207,6 +232,7 @@ struct PlaceParams {
     int32_t slab_rows;           // image rows binned per LDS pass
     uint2 *bucket;               // per workgroup bucket_cap entries: a shower's binned
     int32_t bucket_cap;          //   hits sorted by slab (images of many slabs), or null
+    unsigned long long *clk;     // 2 * CLK_SLOTS stamps, or null
 };
 
 // Device counters of one call: a block for the whole call, then one block

@@ -391,6 +391,7 @@ __attribute__((amdgpu_waves_per_eu((!KEYS && MODE == PM_HITS) ? 8 : 1))) supa_pl
     __shared__ int clist[PL_CLIST];
     // records are valid only when the propagation succeeded; hit outputs
     // only when they all fit
+    stamp_start(Q.clk);
     if (batch_failed(Q.ctr)) return;
     const bool hits = Q.hx != nullptr, img = MODE != PM_HITS && Q.images != nullptr;
     if (hits && (int64_t)Q.sub[SUB_HITS] > Q.hcap) return;
@@ -576,6 +577,7 @@ __attribute__((amdgpu_waves_per_eu((!KEYS && MODE == PM_HITS) ? 8 : 1))) supa_pl
         }
         lds_barrier();
     }
+    stamp_end(Q.clk);
 }
 
 // rows of one LDS slab: whole layers when they fit, else bands of rows

@@ -1151,9 +1151,11 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
 // Start of a call: counters cleared, and the sub-batches' input / output
 // blocks written from the launch's arguments (a copy from the host would be
 // one more step of the call's chain).
-__global__ void supa_begin(unsigned long long *ctr, Cold *cold, ColdBlocks blocks, int n_cold) {
+__global__ void supa_begin(unsigned long long *ctr, Cold *cold, ColdBlocks blocks, int n_cold,
+                           unsigned long long *clk) {
     for (int q = threadIdx.x; q < CTR_WORDS; q += blockDim.x) ctr[q] = 0ull;
     if ((int)threadIdx.x < n_cold) cold[threadIdx.x] = blocks.c[threadIdx.x];
+    if (clk && threadIdx.x == 0) stamp(clk, CLK_BEGIN);
 }
 
 // the node-log chunks claimed so far, noted for a sub-batch
@@ -1181,10 +1183,11 @@ __global__ void supa_azimuth_kernel(const uint32_t *w, int64_t n, float *s, floa
 // ---------------------------------------------------------------------------
 // host-side launchers (called by the C ABI in supa_api.hip)
 // ---------------------------------------------------------------------------
-hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold, hipStream_t s) {
+hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold,
+                        unsigned long long *clk, hipStream_t s) {
     ColdBlocks blocks{};
     for (int j = 0; j < n_cold; ++j) blocks.c[j] = h_cold[j];
-    hipLaunchKernelGGL(supa_begin, dim3(1), dim3(256), 0, s, ctr, cold, blocks, n_cold);
+    hipLaunchKernelGGL(supa_begin, dim3(1), dim3(256), 0, s, ctr, cold, blocks, n_cold, clk);
     return hipGetLastError();
 }
 

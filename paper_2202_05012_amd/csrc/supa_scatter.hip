@@ -54,6 +54,7 @@ __device__ __forceinline__ long long block_excl_scan_ll(long long v, long long *
 
 // tile sums of the hit and node counts
 __global__ void __launch_bounds__(SCAN_THREADS) scan_tiles(ScanParams S) {
+    if (S.clk && threadIdx.x == 0 && blockIdx.x == 0) stamp(S.clk, CLK_SCAN);
     __shared__ long long sh[SCAN_THREADS / 64];
     const int64_t t0 = (int64_t)blockIdx.x * SCAN_TILE;
     long long h = 0, nn = 0;
@@ -92,6 +93,7 @@ __device__ __forceinline__ void publish_counters(const ScanParams &S) {
 // chain of short launches: 4 us each and as much between them).  Wave w scans
 // 64 * ceil(n / 1024) consecutive showers, their counts held in registers.
 __global__ void __launch_bounds__(1024) scan_one(ScanParams S) {
+    if (S.clk && threadIdx.x == 0) stamp(S.clk, CLK_SCAN);
     __shared__ long long sh[2][16];
     const int lane = (int)(threadIdx.x & 63), w = (int)threadIdx.x >> 6;
     const int per = (S.n + 1023) / 1024;
@@ -196,6 +198,7 @@ constexpr int SCATTER_THREADS = 256;
 constexpr int SCATTER_UNROLL = 4;      // records per thread in flight
 
 __global__ void __launch_bounds__(SCATTER_THREADS) scatter_nodes(ScatterParams Q, int32_t n) {
+    stamp_start(Q.clk);
     if (batch_failed(Q.ctr) || (int64_t)Q.sub[SUB_NODES] > Q.ncap) return;
     // the chunks this sub-batch's propagation claimed
     const int c_end = (int)min(Q.sub[SUB_NCHUNK_END], (unsigned long long)Q.n_chunks);
@@ -249,6 +252,7 @@ __global__ void __launch_bounds__(SCATTER_THREADS) scatter_nodes(ScatterParams Q
             }
         }
     }
+    stamp_end(Q.clk);
 }
 
 // ---------------------------------------------------------------------------
