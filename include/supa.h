@@ -237,6 +237,17 @@ supa_status supa_simulate(supa_ctx *ctx, const supa_batch *b, uint64_t seed,
                           supa_output *out);
 
 /*
+ * After a supa_simulate on this context that returned CAPACITY, and nothing
+ * else since: places its records, which are still in the library's logs, into
+ * larger arrays.  The results are those of the whole call repeated.  `out` as
+ * in that call (ledger, counts, offsets and images unchanged: the same
+ * memory), but for the record arrays and their capacities.  Returns OK,
+ * CAPACITY (still too small: may be called again), INVALID_ARG, or STATE when
+ * there is no such call.
+ */
+supa_status supa_place_again(supa_ctx *ctx, supa_output *out);
+
+/*
  * k calls in one (a workload whose outputs do not fit one call, run slice
  * by slice): the same as supa_simulate(ctx, &b[j], seed, &out[j]) for j = 0
  * .. k-1, with one synchronisation at the end, and the propagation of call

@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -105,6 +106,7 @@ static hipError_t fixed_scratch(int device, void **ptr) {
 // threshold table: 4 rings x 64 planes (the propagation kernel's layout)
 constexpr int THR_ENTRIES = 4 * 64;
 
+struct Plan;
 struct supa_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -123,7 +125,7 @@ struct supa_ctx {
     uint64_t *d_c1 = nullptr, *d_c2 = nullptr;
     unsigned long long *d_ctr = nullptr;
     unsigned long long *h_ctr = nullptr;   // pinned
-    unsigned long long *d_clk = nullptr;   // time stamps of a call's kernels
+    unsigned long long *d_clk = nullptr;   // time stamps of a call's kernels (behind d_ctr)
     supa::Cold *d_cold = nullptr;          // per-sub-batch inputs/outputs blocks (device)
     supa::Cold *h_cold = nullptr;          // their pinned host staging copy
     // launch settings and scratch
@@ -176,6 +178,7 @@ struct supa_ctx {
     hipEvent_t ev_place[supa::MAX_SUB] = {};      // end of the hit / image placement (aux)
     // propagation, placement + node scatter, whole call, placement alone,
     // node scatter alone (ms, summed over sub-batches)
+    std::shared_ptr<Plan> pending;       // a call that lacked only room for its records
     mutable float timing[5] = {0, 0, 0, 0, 0};
     mutable bool stamped = false;        // timing is still to be taken from d_clk
     std::string err;
@@ -377,9 +380,7 @@ extern "C" supa_status supa_init_geometry(const supa_geometry *g, int device, vo
               hipMemcpy(c->d_layer_planes, lp.data(), lp.size() * sizeof(int32_t),
                         hipMemcpyHostToDevice) == hipSuccess &&
               hipMalloc(&c->d_c2, THR_ENTRIES * sizeof(uint64_t)) == hipSuccess &&
-              hipMalloc(&c->d_ctr, 2 * supa::CTR_WORDS * sizeof(unsigned long long)) == hipSuccess &&
-              hipMalloc(&c->d_clk, supa::CLK_WORDS * sizeof(unsigned long long)) == hipSuccess &&
-              hipMemset(c->d_clk, 0, supa::CLK_WORDS * sizeof(unsigned long long)) == hipSuccess &&
+              hipMalloc(&c->d_ctr, (2 * supa::CTR_WORDS + supa::CLK_WORDS) * sizeof(unsigned long long)) == hipSuccess &&
               hipHostMalloc(&c->h_ctr, supa::CTR_WORDS * sizeof(unsigned long long), 0) == hipSuccess &&
               hipMalloc(&c->d_cold, supa::MAX_SUB * sizeof(supa::Cold)) == hipSuccess &&
               hipMalloc(&c->d_wclk, (size_t)2 * 32 * c->n_cu * sizeof(unsigned long long)) == hipSuccess &&
@@ -388,6 +389,7 @@ extern "C" supa_status supa_init_geometry(const supa_geometry *g, int device, vo
               hipMemcpy(c->d_c1, c1.data(), THR_ENTRIES * sizeof(uint64_t), hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(c->d_c2, c2.data(), THR_ENTRIES * sizeof(uint64_t), hipMemcpyHostToDevice) == hipSuccess;
     // default priority, and no implicit synchronisation with the null stream
+    c->d_clk = ok ? c->d_ctr + 2 * supa::CTR_WORDS : nullptr;
     ok = ok && hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) == hipSuccess;
     for (hipEvent_t *e : {&c->ev_begin, &c->ev_end, &c->ev_joined})
         ok = ok && hipEventCreate(e) == hipSuccess;
@@ -428,7 +430,6 @@ extern "C" supa_status supa_destroy(supa_ctx *c) {
     if (c->d_c2) (void)hipFree(c->d_c2);
     if (c->d_ctr) (void)hipFree(c->d_ctr);
     if (c->h_ctr) (void)hipHostFree(c->h_ctr);
-    if (c->d_clk) (void)hipFree(c->d_clk);
     if (c->d_cold) (void)hipFree(c->d_cold);
     if (c->d_wclk) (void)hipFree(c->d_wclk);
     if (c->h_cold) (void)hipHostFree(c->h_cold);
@@ -494,8 +495,7 @@ extern "C" supa_status supa_last_subtrees(const supa_ctx *c, int64_t *counts5) {
     return SUPA_OK;
 }
 
-// Times of a call whose kernels stamped the clock (after its end).  Stamps
-// older than the call are of earlier ones with more workgroups.
+// Times of a call whose kernels stamped the clock (after its end).
 static void resolve_timing(const supa_ctx *c) {
     if (!c->stamped) return;
     c->stamped = false;
@@ -513,8 +513,8 @@ static void resolve_timing(const supa_ctx *c) {
     for (int a = 0; a < 2; ++a)
         for (int q = 0; q < supa::CLK_SLOTS; ++q) {
             const unsigned long long *t = h + (a == 0 ? supa::CLK_PLACE : supa::CLK_SCATTER) + q;
-            if (t[0] >= scan) first[a] = std::min(first[a], t[0]);
-            if (t[supa::CLK_SLOTS] >= scan) last[a] = std::max(last[a], t[supa::CLK_SLOTS]);
+            if (t[0]) first[a] = std::min(first[a], t[0]);
+            last[a] = std::max(last[a], t[supa::CLK_SLOTS]);
         }
     auto ms = [&](unsigned long long a, unsigned long long b) { return b > a ? (float)((double)(b - a) / rate_khz) : 0.0f; };
     c->timing[0] = ms(begin, scan);
@@ -647,6 +647,7 @@ static supa_status check_call(supa_ctx *c, const supa_batch *b, supa_output *out
 
 // Everything one call launches: parameters and scratch pointers.
 struct Plan {
+    const float *e0;                 // (never read here)
     bool tree, hits_out, images, recs, post;
     int N, nsub, phases;
     int64_t n, waves, img_words;     // waves: what the scratch is sized for
@@ -670,9 +671,11 @@ static constexpr size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 // pieces are sized to fit it (a batch that needs more fails, see finish).
 static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa_output *out, Plan &L,
                            int force_nsub, char *fixed = nullptr, int set = 0) {
+    c->pending.reset();
     const uint32_t outs = c->g.outputs;
     const int64_t n = b->n;
     L.n = n;
+    L.e0 = b->e0;
     L.tree = (outs & SUPA_OUT_TREE) != 0;
     L.hits_out = (outs & SUPA_OUT_HITS) != 0;
     L.images = (outs & SUPA_OUT_IMAGES) != 0;
@@ -904,6 +907,88 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
     return SUPA_OK;
 }
 
+// Sub-batch j after its propagation: the scan (with scan), the placement and
+// the node scatter, all on stream s.
+static supa_status enqueue_post(supa_ctx *c, supa_output *out, const Plan &L, int j, bool scan,
+                                unsigned long long *h_ctr, unsigned long long *clk, hipStream_t s, bool timed,
+                                hipEvent_t *ev_post, hipEvent_t ev_place) {
+    const int64_t o = L.off(j), nj = L.off(j + 1) - o;
+    auto sub_ctr = [&](int k) { return L.ctr + supa::CTR_BLOCK * (1 + k); };
+    const supa::Params &P = L.P;
+    supa::ScanParams SP{};
+    SP.n = (int32_t)nj;
+    SP.counts = out->counts + 6 * o;
+    SP.hoff = L.hits_out ? out->hit_offsets + o : nullptr;
+    SP.noff = L.tree ? out->node_offsets + o : nullptr;
+    SP.partial = L.d_part;
+    SP.sub = sub_ctr(j);
+    SP.prev = j > 0 ? sub_ctr(j - 1) : nullptr;
+    SP.ctr = L.ctr;
+    SP.host = j == L.nsub - 1 ? h_ctr : nullptr;
+    SP.note_chunks = L.tree && L.nsub == 1;
+    SP.clk = clk;
+
+    supa::PlaceParams H{};
+    H.n = (int32_t)nj;
+    H.n_planes = L.N;
+    H.L = c->n_layers;
+    H.nx = c->g.img_nx;
+    H.ny = c->g.img_ny;
+    H.x0 = (float)c->g.img_x0;
+    H.y0 = (float)c->g.img_y0;
+    H.sx = L.images ? (float)(c->g.img_nx / (c->g.img_x1 - c->g.img_x0)) : 0.0f;
+    H.sy = L.images ? (float)(c->g.img_ny / (c->g.img_y1 - c->g.img_y0)) : 0.0f;
+    H.e_unscale = L.e_unscale;
+    H.ctr = L.ctr;
+    H.sub = sub_ctr(j);
+    H.counts = SP.counts;
+    H.hstart = L.d_hstart ? L.d_hstart + o : nullptr;
+    H.hlog = P.hlog;
+    H.hnext = P.hnext;
+    H.h_chunks = P.h_chunks;
+    H.layer = c->d_layer;
+    H.hoff = SP.hoff;
+    H.hcap = L.hits_out ? out->hit_capacity : 0;
+    H.hx = L.hits_out ? out->hit_x : nullptr;
+    H.hy = L.hits_out ? out->hit_y : nullptr;
+    H.he = L.hits_out ? out->hit_e : nullptr;
+    H.hl = L.hits_out ? out->hit_layer : nullptr;
+    H.hk = L.place_keys ? out->hit_key : nullptr;
+    H.images = L.images ? out->images + L.img_words * o : nullptr;
+    H.bucket = L.d_bucket;
+    H.bucket_cap = L.bucket_cap;
+    H.clk = clk ? clk + supa::CLK_PLACE : nullptr;
+
+    supa::ScatterParams Q{};
+    Q.z_first = P.z_first;
+    Q.dz = P.dz;
+    Q.e_unscale = L.e_unscale;
+    Q.ctr = L.ctr;
+    Q.sub = sub_ctr(j);
+    Q.prev = SP.prev;
+    Q.nlog = P.nlog;
+    Q.nfill = P.nfill;
+    Q.n_chunks = P.n_chunks;
+    Q.noff = SP.noff;
+    Q.ncap = L.tree ? out->node_capacity : 0;
+    Q.np = out->node_parent;
+    Q.ng = out->node_gen;
+    Q.nvx = out->node_vx;
+    Q.nvy = out->node_vy;
+    Q.nvz = out->node_vz;
+    Q.ne = out->node_e;
+    Q.nk = (L.tree && P.keys) ? out->node_key : nullptr;
+    Q.clk = clk ? clk + supa::CLK_SCATTER : nullptr;
+
+    if (scan) HIP_TRY(c, supa::launch_scan(SP, s));
+    if (timed) HIP_TRY(c, hipEventRecord(ev_post[0], s));
+    if (L.recs) HIP_TRY(c, supa::launch_place(H, c->n_cu, s));
+    if (timed && L.recs && L.tree) HIP_TRY(c, hipEventRecord(ev_place, s));
+    if (L.tree) HIP_TRY(c, supa::launch_scatter_nodes(Q, (int32_t)nj, c->n_cu, s));
+    if (timed) HIP_TRY(c, hipEventRecord(ev_post[1], s));
+    return SUPA_OK;
+}
+
 // Launches the call: counters cleared, then per sub-batch the work order,
 // the propagation (main stream) and the scan, placement and node scatter
 // (second stream, after the propagation of the same sub-batch).  d_cold
@@ -954,78 +1039,10 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
         if (timed || two) HIP_TRY(c, hipEventRecord(ev_prop[j][1], s_main));
         if (!L.post) continue;
 
-        supa::ScanParams SP{};
-        SP.n = (int32_t)nj;
-        SP.counts = out->counts + 6 * o;
-        SP.hoff = L.hits_out ? out->hit_offsets + o : nullptr;
-        SP.noff = L.tree ? out->node_offsets + o : nullptr;
-        SP.partial = L.d_part;
-        SP.sub = sub_ctr(j);
-        SP.prev = j > 0 ? sub_ctr(j - 1) : nullptr;
-        SP.ctr = L.ctr;
-        SP.host = j == L.nsub - 1 ? h_ctr : nullptr;
-        SP.note_chunks = L.tree && L.nsub == 1;
-        SP.clk = clk;
-
-        supa::PlaceParams H{};
-        H.n = (int32_t)nj;
-        H.n_planes = L.N;
-        H.L = c->n_layers;
-        H.nx = c->g.img_nx;
-        H.ny = c->g.img_ny;
-        H.x0 = (float)c->g.img_x0;
-        H.y0 = (float)c->g.img_y0;
-        H.sx = L.images ? (float)(c->g.img_nx / (c->g.img_x1 - c->g.img_x0)) : 0.0f;
-        H.sy = L.images ? (float)(c->g.img_ny / (c->g.img_y1 - c->g.img_y0)) : 0.0f;
-        H.e_unscale = L.e_unscale;
-        H.ctr = L.ctr;
-        H.sub = sub_ctr(j);
-        H.counts = SP.counts;
-        H.hstart = L.d_hstart ? L.d_hstart + o : nullptr;
-        H.hlog = P.hlog;
-        H.hnext = P.hnext;
-        H.h_chunks = P.h_chunks;
-        H.layer = c->d_layer;
-        H.hoff = SP.hoff;
-        H.hcap = L.hits_out ? out->hit_capacity : 0;
-        H.hx = L.hits_out ? out->hit_x : nullptr;
-        H.hy = L.hits_out ? out->hit_y : nullptr;
-        H.he = L.hits_out ? out->hit_e : nullptr;
-        H.hl = L.hits_out ? out->hit_layer : nullptr;
-        H.hk = L.place_keys ? out->hit_key : nullptr;
-        H.images = L.images ? out->images + L.img_words * o : nullptr;
-        H.bucket = L.d_bucket;
-        H.bucket_cap = L.bucket_cap;
-        H.clk = clk ? clk + supa::CLK_PLACE : nullptr;
-
-        supa::ScatterParams Q{};
-        Q.z_first = P.z_first;
-        Q.dz = P.dz;
-        Q.e_unscale = L.e_unscale;
-        Q.ctr = L.ctr;
-        Q.sub = sub_ctr(j);
-        Q.prev = SP.prev;
-        Q.nlog = P.nlog;
-        Q.nfill = P.nfill;
-        Q.n_chunks = P.n_chunks;
-        Q.noff = SP.noff;
-        Q.ncap = L.tree ? out->node_capacity : 0;
-        Q.np = out->node_parent;
-        Q.ng = out->node_gen;
-        Q.nvx = out->node_vx;
-        Q.nvy = out->node_vy;
-        Q.nvz = out->node_vz;
-        Q.ne = out->node_e;
-        Q.nk = (L.tree && P.keys) ? out->node_key : nullptr;
-        Q.clk = clk ? clk + supa::CLK_SCATTER : nullptr;
-
         if (two) HIP_TRY(c, hipStreamWaitEvent(s_aux, ev_prop[j][1], 0));
-        HIP_TRY(c, supa::launch_scan(SP, s_aux));
-        if (timed) HIP_TRY(c, hipEventRecord(ev_post[j][0], s_aux));
-        if (L.recs) HIP_TRY(c, supa::launch_place(H, c->n_cu, s_aux));
-        if (timed && L.recs && L.tree) HIP_TRY(c, hipEventRecord(ev_place[j], s_aux));
-        if (L.tree) HIP_TRY(c, supa::launch_scatter_nodes(Q, (int32_t)nj, c->n_cu, s_aux));
-        if (timed || two) HIP_TRY(c, hipEventRecord(ev_post[j][1], s_aux));
+        const supa_status st = enqueue_post(c, out, L, j, true, h_ctr, clk, s_aux, timed, ev_post[j], ev_place[j]);
+        if (st != SUPA_OK) return st;
+        if (!timed && two) HIP_TRY(c, hipEventRecord(ev_post[j][1], s_aux));
     }
     if (join && L.post && s_aux != s_main) HIP_TRY(c, hipStreamWaitEvent(s_main, ev_post[L.nsub - 1][1], 0));
     return SUPA_OK;
@@ -1095,6 +1112,15 @@ static void size_logs(supa_ctx *c, const supa_batch *b, const supa_output *out) 
                                node_chunks_for(std::min<int64_t>(out->node_capacity, (int64_t)1 << 28), waves));
 }
 
+// Adds the times (ms) between the events of one sub-batch's enqueue_post.
+static void post_times(const Plan &L, const hipEvent_t *ev_post, hipEvent_t ev_place, float &post, float &place,
+                       float &scatter) {
+    float t = 0;
+    if (L.post && hipEventElapsedTime(&t, ev_post[0], ev_post[1]) == hipSuccess) post += t;
+    if (L.recs && hipEventElapsedTime(&t, ev_post[0], L.tree ? ev_place : ev_post[1]) == hipSuccess) place += t;
+    if (L.tree && hipEventElapsedTime(&t, L.recs ? ev_place : ev_post[0], ev_post[1]) == hipSuccess) scatter += t;
+}
+
 // Runs a prepared call once: launches it, reads back its counters (one
 // synchronisation) and records the kernel times.
 static supa_status run_once(supa_ctx *c, const supa_batch *b, supa_output *out, const Plan &L) {
@@ -1119,11 +1145,7 @@ static supa_status run_once(supa_ctx *c, const supa_batch *b, supa_output *out, 
     float t_prop = 0, t_post = 0, t_all = 0, t_place = 0, t_scatter = 0, t = 0;
     for (int j = 0; j < L.nsub; ++j) {
         if (hipEventElapsedTime(&t, c->ev_prop[j][0], c->ev_prop[j][1]) == hipSuccess) t_prop += t;
-        if (L.post && hipEventElapsedTime(&t, c->ev_post[j][0], c->ev_post[j][1]) == hipSuccess) t_post += t;
-        if (L.recs && hipEventElapsedTime(&t, c->ev_post[j][0], L.tree ? c->ev_place[j] : c->ev_post[j][1]) == hipSuccess)
-            t_place += t;
-        if (L.tree && hipEventElapsedTime(&t, L.recs ? c->ev_place[j] : c->ev_post[j][0], c->ev_post[j][1]) == hipSuccess)
-            t_scatter += t;
+        post_times(L, c->ev_post[j], c->ev_place[j], t_post, t_place, t_scatter);
     }
     (void)hipEventElapsedTime(&t_all, c->ev_begin, c->ev_end);
     (void)hipGetLastError();
@@ -1148,9 +1170,48 @@ extern "C" supa_status supa_simulate(supa_ctx *c, const supa_batch *b, uint64_t 
         st = run_once(c, b, out, L);
         if (st != SUPA_OK) return st;
         const int r = finish(c, L, out);
+        if (r == SUPA_ERR_CAPACITY) c->pending = std::make_shared<Plan>(L);
         if (r >= 0) return (supa_status)r;
     }
     return fail(c, SUPA_ERR_NOMEM, "scratch sizes did not converge");
+}
+
+// The records of the last call, still in the logs, into larger arrays.
+extern "C" supa_status supa_place_again(supa_ctx *c, supa_output *out) {
+    if (!c) return SUPA_ERR_STATE;
+    if (c->broken) return fail(c, SUPA_ERR_STATE, "context unusable after a device error");
+    if (!c->pending) return fail(c, SUPA_ERR_STATE, "the last call on this context did not return CAPACITY");
+    c->err.clear();
+    const Plan &L = *c->pending;
+    supa_batch b{};
+    b.e0 = b.polar = b.azimuth = L.e0;
+    b.n = L.n;
+    std::string why;
+    const supa_status v = check_args(c->g.outputs, &b, out, why);
+    if (v != SUPA_OK) return fail(c, v, why);
+    if (L.place_keys != (L.hits_out && (c->g.outputs & SUPA_OUT_KEYS) && out->hit_key != nullptr))
+        return fail(c, SUPA_ERR_INVALID_ARG, "hit_key given to one of the two calls only");
+    HIP_TRY(c, hipSetDevice(c->device));
+    out->total_hits = out->total_nodes = out->total_steps = 0;
+    const int r = finish(c, L, out);
+    if (r != SUPA_OK) return (supa_status)r;
+    const bool timed = !c->stamped;
+    float post = 0, place = 0, scatter = 0;
+    for (int j = 0; j < L.nsub; ++j) {
+        const supa_status st = enqueue_post(c, out, L, j, false, nullptr, timed ? nullptr : c->d_clk, c->stream, timed,
+                                            c->ev_post[j], c->ev_place[j]);
+        if (st != SUPA_OK) return st;
+    }
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    for (int j = 0; timed && j < L.nsub; ++j) post_times(L, c->ev_post[j], c->ev_place[j], post, place, scatter);
+    if (timed) {
+        c->timing[1] = post;
+        c->timing[2] += post;
+        c->timing[3] = place;
+        c->timing[4] = scatter;
+    }
+    c->pending.reset();
+    return SUPA_OK;
 }
 
 // supa_simulate with the library's scratch carved out of this device's fixed
@@ -1275,9 +1336,8 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
         for (int32_t j = 0; j < k; ++j) {
             const hipEvent_t *e = &c->call_ev[(size_t)j * 5];
             if (hipEventElapsedTime(&t, e[0], e[1]) == hipSuccess) t_prop += t;
-            if (plans[j].post && hipEventElapsedTime(&t, e[2], e[4]) == hipSuccess) t_post += t;
-            if (plans[j].recs && hipEventElapsedTime(&t, e[2], e[plans[j].tree ? 3 : 4]) == hipSuccess) t_place += t;
-            if (plans[j].tree && hipEventElapsedTime(&t, e[plans[j].recs ? 3 : 2], e[4]) == hipSuccess) t_scatter += t;
+            const hipEvent_t ev_post[2] = {e[2], e[4]};
+            post_times(plans[j], ev_post, e[3], t_post, t_place, t_scatter);
         }
         (void)hipEventElapsedTime(&t_all, c->ev_begin, c->ev_end);
         (void)hipGetLastError();
@@ -1387,6 +1447,7 @@ extern "C" supa_status supa_graph_launch(supa_graph *g, void *hip_stream) {
     const supa_status cur = graph_current(g);
     if (cur != SUPA_OK) return cur;
     HIP_TRY(c, hipSetDevice(c->device));
+    c->pending.reset();                  // (the graph writes the same logs)
     HIP_TRY(c, hipGraphLaunch(g->exec, hip_stream ? (hipStream_t)hip_stream : c->stream));
     return SUPA_OK;
 }

@@ -1155,7 +1155,10 @@ __global__ void supa_begin(unsigned long long *ctr, Cold *cold, ColdBlocks block
                            unsigned long long *clk) {
     for (int q = threadIdx.x; q < CTR_WORDS; q += blockDim.x) ctr[q] = 0ull;
     if ((int)threadIdx.x < n_cold) cold[threadIdx.x] = blocks.c[threadIdx.x];
-    if (clk && threadIdx.x == 0) stamp(clk, CLK_BEGIN);
+    if (!clk) return;
+    for (int q = threadIdx.x; q < CLK_WORDS; q += blockDim.x) clk[q] = 0ull;
+    __syncthreads();
+    if (threadIdx.x == 0) stamp(clk, CLK_BEGIN);
 }
 
 // the node-log chunks claimed so far, noted for a sub-batch

@@ -73,7 +73,7 @@ class Output(C.Structure):
 
 
 EXPORTS = ["supa_abi_version", "supa_validate_geometry", "supa_validate_call", "supa_init_geometry", "supa_destroy",
-           "supa_simulate", "supa_simulate_batches", "supa_simulate_noalloc", "supa_set_launch", "supa_set_schedule", "supa_set_subtrees", "supa_last_subtrees", "supa_autotune", "supa_autotune_forget",
+           "supa_simulate", "supa_place_again", "supa_simulate_batches", "supa_simulate_noalloc", "supa_set_launch", "supa_set_schedule", "supa_set_subtrees", "supa_last_subtrees", "supa_autotune", "supa_autotune_forget",
            "supa_graph_create", "supa_graph_launch", "supa_graph_check", "supa_graph_destroy", "supa_last_timing", "supa_last_kernel_times", "supa_last_wave_times", "supa_philox", "supa_azimuth",
            "supa_last_error"]
 
@@ -100,6 +100,8 @@ def load():
         L.supa_destroy.argtypes = [C.c_void_p]
         L.supa_simulate.restype = C.c_int
         L.supa_simulate.argtypes = [C.c_void_p, C.POINTER(Batch), C.c_uint64, C.POINTER(Output)]
+        L.supa_place_again.restype = C.c_int
+        L.supa_place_again.argtypes = [C.c_void_p, C.POINTER(Output)]
         L.supa_simulate_batches.restype = C.c_int
         L.supa_simulate_batches.argtypes = [C.c_void_p, C.c_int32, C.POINTER(Batch), C.c_uint64,
                                             C.POINTER(Output)]
@@ -481,7 +483,11 @@ class Simulator:
             for k in self._PER_HIT + self._PER_NODE + ("hit_capacity", "node_capacity"):
                 if k in grown:
                     out[k] = grown[k]
-            st = self.run(e0, polar, azimuth, seed, out, x0, y0, shower_id_base)
+            # the records are still in the library's logs: placed again (the
+            # propagation and the segment offsets stand)
+            _, o = self._marshal(e0, polar, azimuth, out, x0, y0, shower_id_base)
+            st = self.lib.supa_place_again(self.ctx, C.byref(o))
+            self._totals(out, o)
             self._check(st)
         th, tn = out["total_hits"], out["total_nodes"]
         for k in ("hit_x", "hit_y", "hit_e", "hit_layer", "hit_key"):
