@@ -77,16 +77,26 @@ __global__ void __launch_bounds__(SCAN_THREADS) scan_tiles(ScanParams S) {
 // After the scan (one block): the chunks claimed so far, and the call's
 // counters to the host.  Nothing later in the call writes them, so the host
 // need not copy them back: a copy of 5 KB between two kernels and the
-// synchronisation took 10 to 15 us.
+// synchronisation took 10 to 15 us.  System-scope stores go through the caches
+// and are complete when the kernel ends; a fence would write the whole L2 back
+// first (the logs are in it: 9 us).  The particle-steps' copies are summed.
 __device__ __forceinline__ void publish_counters(const ScanParams &S) {
     if (S.note_chunks && threadIdx.x == 0) S.sub[SUB_NCHUNK_END] = S.ctr[CTR_NCHUNK];
     if (!S.host) return;
-    __threadfence();
-    __syncthreads();
-    for (int q = (int)threadIdx.x; q < CTR_WORDS; q += (int)blockDim.x)
-        __hip_atomic_store(S.host + q, __hip_atomic_load(S.ctr + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __threadfence_system();
+    __syncthreads();                      // the totals, stored by thread 0
+    auto word = [&](int q) { return __hip_atomic_load(S.ctr + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto put = [&](int q, unsigned long long v) {
+        __hip_atomic_store(S.host + q, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    static_assert(STEP_COPIES <= 64 && CTR_STEPS <= 1024, "one word per thread");
+    if ((int)threadIdx.x < CTR_STEPS) put((int)threadIdx.x, word((int)threadIdx.x));
+    if (threadIdx.x < 64) {
+        unsigned long long t = (int)threadIdx.x < STEP_COPIES ? word(CTR_STEPS + (int)threadIdx.x * STEP_STRIDE) : 0ull;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+        if ((int)threadIdx.x < STEP_COPIES)
+            put(CTR_STEPS + (int)threadIdx.x * STEP_STRIDE, threadIdx.x == 0 ? t : 0ull);
+    }
 }
 
 // Up to SCAN_ONE showers: all of it by one block (a call of 1,000 showers is a
