@@ -1252,20 +1252,51 @@ __global__ void scatter_rows_kernel(int m, int w, const int32_t *idx, const floa
 }
 
 // per-row sums of groups: out[b][l] = sum_{q < g} x[b][l*g + q]
-// one wave per group: its lanes read the group's g values with unit stride
-// (coalesced) and the partial sums meet in a butterfly reduction
-constexpr int GS_WAVES = 4;
-__global__ void __launch_bounds__(64 * GS_WAVES) group_sums_kernel(int rows, int L, int g, const float *x,
-                                                                  float *out) {
-    const int64_t t = (int64_t)blockIdx.x * GS_WAVES + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (t >= (int64_t)rows * L) return;              // whole waves leave together
-    const float *p = x + t * g;
-    float s = 0.f;
-    for (int q = lane; q < g; q += 64) s += p[q];
+// W lanes per group (the power of two that holds g, at most a wave): they read
+// the group's values with unit stride (coalesced) and the partial sums meet in
+// a butterfly reduction.  A wave takes GS_UNROLL steps of 64 / W groups, all
+// loads first (sixteen values per lane in flight).  Bound by the read of x:
+// 163,840 groups of 256 in 25 us, 6.7 TB/s from the last-level cache (one wave
+// per group, its loads one after the other: 56 us), 400,000 groups of one
+// 5 us (56).  Every group's sum has the same order whatever W is.
+constexpr int GS_THREADS = 256, GS_UNROLL = 4;
+
+template <int W>
+__global__ void __launch_bounds__(GS_THREADS) group_sums_kernel(int64_t groups, int g, const float *x, float *out) {
+    constexpr int per_wave = 64 / W * GS_UNROLL;
+    const int64_t wave = ((int64_t)blockIdx.x * GS_THREADS + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63, sub = lane / W, q0 = lane % W;
+    const int64_t t0 = wave * per_wave + sub;
+    float s[GS_UNROLL];
+    const float *p[GS_UNROLL];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) out[t] = s;
+    for (int u = 0; u < GS_UNROLL; ++u) {
+        const int64_t t = t0 + u * (64 / W);
+        s[u] = 0.f;
+        p[u] = x + (t < groups ? t : groups - 1) * g;
+    }
+    int q = q0;
+    for (; q + 3 * W < g; q += 4 * W) {
+        float v[4][GS_UNROLL];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int u = 0; u < GS_UNROLL; ++u) v[k][u] = p[u][q + k * W];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int u = 0; u < GS_UNROLL; ++u) s[u] += v[k][u];
+    }
+    for (; q < g; q += W)
+#pragma unroll
+        for (int u = 0; u < GS_UNROLL; ++u) s[u] += p[u][q];
+#pragma unroll
+    for (int u = 0; u < GS_UNROLL; ++u) {
+#pragma unroll
+        for (int off = W / 2; off > 0; off >>= 1) s[u] += __shfl_xor(s[u], off);
+        const int64_t t = t0 + u * (64 / W);
+        if (q0 == 0 && t < groups) out[t] = s[u];
+    }
 }
 
 hipError_t launch_select(int n, const float *v, float tau, int32_t *idx, int32_t *count,
@@ -1301,8 +1332,17 @@ hipError_t launch_scatter_rows(int m, int w, const int32_t *idx, const float *sr
 hipError_t launch_group_sums(int rows, int L, int g, const float *x, float *out, hipStream_t s) {
     const int64_t t = (int64_t)rows * L;
     if (t <= 0) return hipSuccess;
-    hipLaunchKernelGGL(group_sums_kernel, dim3((unsigned)((t + GS_WAVES - 1) / GS_WAVES)), dim3(64 * GS_WAVES),
-                       0, s, rows, L, g, x, out);
+    auto go = [&](auto kernel, int w) {
+        const int64_t per = (int64_t)(GS_THREADS / w) * GS_UNROLL;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((t + per - 1) / per)), dim3(GS_THREADS), 0, s, t, g, x, out);
+    };
+    if (g == 1) go(group_sums_kernel<1>, 1);
+    else if (g == 2) go(group_sums_kernel<2>, 2);
+    else if (g <= 4) go(group_sums_kernel<4>, 4);
+    else if (g <= 8) go(group_sums_kernel<8>, 8);
+    else if (g <= 16) go(group_sums_kernel<16>, 16);
+    else if (g <= 32) go(group_sums_kernel<32>, 32);
+    else go(group_sums_kernel<64>, 64);
     return hipGetLastError();
 }
 
