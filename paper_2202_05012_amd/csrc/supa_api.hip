@@ -20,8 +20,8 @@
 #include "supa_device.hpp"
 
 namespace supa {
-hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold,
-                        unsigned long long *clk, hipStream_t s);
+hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold, unsigned long long *clk,
+                        const float *e0, int n, float e_scale, int32_t *order, hipStream_t s);
 hipError_t launch_note_chunks(const unsigned long long *ctr, unsigned long long *sub, hipStream_t s);
 hipError_t launch_propagate(const Params &P, bool literal, bool rings, int blocks, hipStream_t s);
 hipError_t launch_philox(const uint32_t *ctr, int64_t n, uint32_t k0, uint32_t k1, uint32_t *out,
@@ -35,7 +35,7 @@ hipError_t launch_scan(const ScanParams &S, hipStream_t s);
 hipError_t launch_scatter_nodes(const ScatterParams &Q, int32_t n, int n_cu, hipStream_t s);
 int64_t order_scratch_words();
 hipError_t launch_cost_order(const float *e0, int n, float e_scale, uint32_t *hist, int32_t *order,
-                             int n_cu, hipStream_t s);
+                             int n_cu, unsigned long long *clk, hipStream_t s);
 }  // namespace supa
 
 // A device buffer that only grows (its contents are scratch).  Every
@@ -519,7 +519,7 @@ static void resolve_timing(const supa_ctx *c) {
     auto ms = [&](unsigned long long a, unsigned long long b) { return b > a ? (float)((double)(b - a) / rate_khz) : 0.0f; };
     c->timing[0] = ms(begin, scan);
     c->timing[1] = ms(std::min(first[0], first[1]), std::max(last[0], last[1]));
-    c->timing[2] = ms(begin, std::max({scan, last[0], last[1]}));
+    c->timing[2] = ms(h[supa::CLK_CALL], std::max({scan, last[0], last[1]}));
     c->timing[3] = ms(first[0], last[0]);
     c->timing[4] = ms(first[1], last[1]);
 }
@@ -707,7 +707,14 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
     // spill; image buckets; hit and node logs
     const size_t hstart_b = L.recs ? al256((size_t)n * 8) : 0;
     const size_t part_b = al256((size_t)supa::scan_partial_words(n) * 8);
-    const bool ordered = c->cost_order > 0 || (c->cost_order < 0 && n >= kAutoOrderMin);
+    // Automatic work order: when showers have to wait for a wave, and can differ
+    // much (the planes bound a shower's size); the propagation of 20,000 showers
+    // of 1 to 1000 units took 1,600 us in batch order, 683 in this one; of 8,192
+    // of 1 to 100 units 194 and 157; at one shower per wave and less it gains
+    // nothing but costs its 4 to 8 us.  The fixed array's layout knows the old
+    // limit only, and every sub-batch orders with launches of its own.
+    const bool auto_order = n >= kAutoOrderMin || (!fixed && nsub <= 1 && n > L.waves && L.N > 8);
+    const bool ordered = c->cost_order > 0 || (c->cost_order < 0 && auto_order);
     const size_t order_b = ordered ? al256((size_t)n * 4) + al256((size_t)supa::order_scratch_words() * 4) : 0;
     const size_t shower_b = hstart_b + part_b + order_b;
     int64_t bucket_per = 0, bucket_blocks = 0;
@@ -1007,7 +1014,13 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
                            bool join = true) {
     auto sub_ctr = [&](int j) { return L.ctr + supa::CTR_BLOCK * (1 + j); };
     const supa::Params &P = L.P;
-    HIP_TRY(c, supa::launch_begin(L.ctr, d_cold, h_cold, h_cold ? L.nsub : 0, clk, s_main));
+    // the work order of a call's only sub-batch comes first (few showers: in
+    // the same kernel), those of several before their propagation
+    const bool order_first = L.d_order && L.nsub == 1;
+    if (order_first && L.n > supa::ORDER_ONE)
+        HIP_TRY(c, supa::launch_cost_order(b->e0, (int)L.n, P.e_scale, L.d_ohist, L.d_order, c->n_cu, clk, s_main));
+    HIP_TRY(c, supa::launch_begin(L.ctr, d_cold, h_cold, h_cold ? L.nsub : 0, clk, b->e0, (int)L.n, P.e_scale,
+                                  order_first ? L.d_order : nullptr, s_main));
     for (int j = 0; j < L.nsub; ++j) {
         const int64_t o = L.off(j), nj = L.off(j + 1) - o;
         supa::Params Pj = P;
@@ -1015,9 +1028,9 @@ static supa_status enqueue(supa_ctx *c, const supa_batch *b, supa_output *out, c
         Pj.sid_base = b->shower_id_base + (uint32_t)o;
         Pj.cold = d_cold + j;
         Pj.sub = sub_ctr(j);
-        if (L.d_order)
+        if (L.d_order && !order_first)
             HIP_TRY(c, supa::launch_cost_order(b->e0 + o, (int)nj, P.e_scale, L.d_ohist, L.d_order + o,
-                                               c->n_cu, s_main));
+                                               c->n_cu, nullptr, s_main));
         if (timed) HIP_TRY(c, hipEventRecord(ev_prop[j][0], s_main));
         // up to kExpand pending particles and a step's daughters in LDS, where
         // breadth first can take them in order
@@ -1125,10 +1138,9 @@ static void post_times(const Plan &L, const hipEvent_t *ev_post, hipEvent_t ev_p
 // synchronisation) and records the kernel times.
 static supa_status run_once(supa_ctx *c, const supa_batch *b, supa_output *out, const Plan &L) {
     // One sub-batch: nothing would overlap on a second stream, so all of it is
-    // one chain on the caller's, and its kernels take the times (with a work
-    // order, which belongs to no part, the call is long and events do).
+    // one chain on the caller's, and its kernels take the times.
     const bool one = L.nsub == 1;
-    const bool stamps = one && L.post && !L.d_order;
+    const bool stamps = one && L.post;
     if (!stamps) HIP_TRY(c, hipEventRecord(c->ev_begin, c->stream));
     supa_status st = enqueue(c, b, out, L, c->d_cold, c->h_cold, L.post ? c->h_ctr : nullptr,
                              stamps ? c->d_clk : nullptr, c->stream, one ? c->stream : c->aux, !stamps,

@@ -170,6 +170,8 @@ struct ScanParams {
     unsigned long long *clk;          // CLK_SCAN is stamped here, or null
 };
 
+constexpr int ORDER_ONE = 32 * 1024;     // showers that the call's first kernel can order
+
 // Device times of a call that is one chain of kernels: the kernels store the
 // device's wall clock.  (An event between two kernels is
 // a packet of its own, with a cache write-back: about 5 us each, a quarter of
@@ -177,8 +179,9 @@ struct ScanParams {
 // last one to end last.
 constexpr int CLK_SLOTS = 64;
 enum {
-    CLK_BEGIN = 0,       // counters cleared
+    CLK_BEGIN = 0,       // counters cleared, work ordered: the propagation may start
     CLK_SCAN = 1,        // the scan starts: the propagation is done
+    CLK_CALL = 2,        // the call's first kernel
     CLK_PLACE = 8,       // placement: starts, then ends
     CLK_SCATTER = CLK_PLACE + 2 * CLK_SLOTS,
     CLK_WORDS = CLK_SCATTER + 2 * CLK_SLOTS

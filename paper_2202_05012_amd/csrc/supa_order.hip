@@ -7,8 +7,9 @@
 // launch, so no wave starts a long shower when the others are done (longest
 // processing time first).  The order is a counting sort of the showers by
 // a bucket of log2 of their fixed-point energy, descending: three kernels
-// (histogram, scan of the buckets, scatter).  The order within a bucket is
-// arbitrary; results do not depend on the order at all.
+// (histogram, scan of the buckets, scatter), or, up to ORDER_ONE showers, one
+// block of the kernel that starts the call anyway.  The order within a bucket
+// is arbitrary; results do not depend on the order at all.
 #include <algorithm>
 
 #include "supa_device.hpp"
@@ -79,19 +80,102 @@ __global__ void __launch_bounds__(ORDER_THREADS) order_scatter(const float *e0, 
     }
 }
 
-__global__ void order_clear(uint32_t *hist) {
+__global__ void order_clear(uint32_t *hist, unsigned long long *clk) {
+    if (clk && blockIdx.x == 0 && threadIdx.x == 0) stamp(clk, CLK_CALL);
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q < ORDER_BUCKETS) hist[q] = 0u;
+}
+
+// Start of a call: counters cleared, and the sub-batches' input / output
+// blocks written from the launch's arguments (a copy from the host would be
+// one more step of the call's chain).  With ORDER also the work order of its
+// n <= ORDER_ONE showers, by the same block: their buckets in registers, ranks
+// from the LDS counts.
+template <bool ORDER>
+__global__ void __launch_bounds__(ORDER ? 1024 : 256)
+    supa_begin(unsigned long long *ctr, Cold *cold, ColdBlocks blocks, int n_cold, unsigned long long *clk,
+               const float *e0, int n, float e_scale, int32_t *order) {
+    __shared__ uint32_t h[ORDER ? ORDER_BUCKETS : 1], sums[16];
+    const int t = (int)threadIdx.x;
+    if (clk) {
+        for (int q = t; q < CLK_WORDS; q += blockDim.x)
+            if (q != CLK_CALL) clk[q] = 0ull;
+        // (a work order by kernels of its own has stamped the start)
+        if (t == 0 && (ORDER || !order)) stamp(clk, CLK_CALL);
+    }
+    for (int q = t; q < CTR_WORDS; q += blockDim.x) ctr[q] = 0ull;
+    if (t < n_cold) cold[t] = blocks.c[t];
+    if constexpr (ORDER) {
+        constexpr int PER = ORDER_ONE / 1024;
+        static_assert(ORDER_BUCKETS == 1024, "one bucket per thread");
+        h[t] = 0u;
+        __syncthreads();
+        int b[PER];
+        uint32_t rank[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) b[q] = t + 1024 * q < n ? cost_bucket(e0[t + 1024 * q], e_scale) : -1;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            // one atomic for the lanes that share the first lane's bucket (all
+            // of them in a batch of one energy: 64 in turn on one counter)
+            if (1024 * q >= n) continue;
+            const int b0 = __builtin_amdgcn_readfirstlane(b[q]);
+            const uint64_t same = __ballot(b[q] == b0 && b0 >= 0);
+            uint32_t base = 0u;
+            if (same && (t & 63) == 0) base = atomicAdd(&h[b0], (uint32_t)__builtin_popcountll(same));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (b[q] == b0)
+                rank[q] = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0));
+            else
+                rank[q] = b[q] >= 0 ? atomicAdd(&h[b[q]], 1u) : 0u;
+        }
+        __syncthreads();
+        // bucket counts -> starts
+        const uint32_t v = h[t];
+        uint32_t incl = v;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(incl, off, 64);
+            if ((t & 63) >= off) incl += o;
+        }
+        if ((t & 63) == 63) sums[t >> 6] = incl;
+        __syncthreads();
+        uint32_t before = 0u;
+        for (int w = 0; w < (t >> 6); ++w) before += sums[w];
+        h[t] = before + incl - v;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (1024 * q < n && b[q] >= 0) order[h[b[q]] + rank[q]] = t + 1024 * q;
+    }
+    if (!clk) return;
+    __syncthreads();
+    if (t == 0) stamp(clk, CLK_BEGIN);
+}
+
+// order: null, or the array for the work order of n showers; written here when
+// n <= ORDER_ONE, else already there.
+hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold, unsigned long long *clk,
+                        const float *e0, int n, float e_scale, int32_t *order, hipStream_t s) {
+    ColdBlocks blocks{};
+    for (int j = 0; j < n_cold; ++j) blocks.c[j] = h_cold[j];
+    if (order && n <= ORDER_ONE)
+        hipLaunchKernelGGL(supa_begin<true>, dim3(1), dim3(1024), 0, s, ctr, cold, blocks, n_cold, clk, e0, n,
+                           e_scale, order);
+    else
+        hipLaunchKernelGGL(supa_begin<false>, dim3(1), dim3(256), 0, s, ctr, cold, blocks, n_cold, clk, e0, n,
+                           e_scale, order);
+    return hipGetLastError();
 }
 
 int64_t order_scratch_words() { return ORDER_BUCKETS; }
 
 // order[0..n) = a permutation of 0..n-1, most expensive first; hist: ORDER_BUCKETS words
 hipError_t launch_cost_order(const float *e0, int n, float e_scale, uint32_t *hist, int32_t *order,
-                             int n_cu, hipStream_t s) {
+                             int n_cu, unsigned long long *clk, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int blocks = std::max(1, std::min((n + ORDER_THREADS - 1) / ORDER_THREADS, n_cu * 4));
-    hipLaunchKernelGGL(order_clear, dim3(ORDER_BUCKETS / 256), dim3(256), 0, s, hist);
+    hipLaunchKernelGGL(order_clear, dim3(ORDER_BUCKETS / 256), dim3(256), 0, s, hist, clk);
     hipLaunchKernelGGL(order_hist, dim3(blocks), dim3(ORDER_THREADS), 0, s, e0, n, e_scale, hist);
     hipLaunchKernelGGL(order_scan, dim3(1), dim3(ORDER_BUCKETS), 0, s, hist);
     hipLaunchKernelGGL(order_scatter, dim3((n + ORDER_RUN - 1) / ORDER_RUN), dim3(ORDER_THREADS), 0, s, e0, n,

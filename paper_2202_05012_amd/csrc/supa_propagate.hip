@@ -585,21 +585,31 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
             }
             if (b_at == b_left) {
                 const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_base);
-                if (base >= (uint32_t)P.n) {
+                const uint32_t first = (uint32_t)P.waves * (uint32_t)P.claim0;
+                const auto ord = COLD(order);
+                // with a work order the first batches are dealt out: the most
+                // expensive showers to one wave each, there and back, not
+                // claim0 neighbours to every wave
+                const bool dealt = ord && base < first;
+                if (!dealt && base >= (uint32_t)P.n) {
                     exhausted = true;
                     break;
                 }
-                const uint32_t first = (uint32_t)P.waves * (uint32_t)P.claim0;
                 next_base = 0xffffffffu;
                 if (first < (uint32_t)P.n && lane == 0)
                     next_base = (uint32_t)min<unsigned long long>(
                         first + atomicAdd(&P.sub[SUB_WORK], (unsigned long long)P.claim1), 0xffffffffull);
-                b_left = min(base < first ? P.claim0 : P.claim1, P.n - (int)base);
+                int item = (int)base + (int)lane;
+                if (dealt) {
+                    item = (int)lane * P.waves + (((int)lane & 1) ? P.waves - 1 - (int)wave : (int)wave);
+                    b_left = (int)__builtin_popcountll(wave_ballot((int)lane < P.claim0 && item < P.n));
+                } else {
+                    b_left = min(base < first ? P.claim0 : P.claim1, P.n - (int)base);
+                }
                 b_at = 0;
+                if (b_left == 0) continue;
                 if ((int)lane < b_left) {
                     // initial condition (section "Using SUPA": energy, angle, impact point)
-                    const int item = (int)base + (int)lane;
-                    const auto ord = COLD(order);
                     const int i = ord ? ord[item] : item;
                     const float sc = COLD(e0)[i] * P.e_scale;
                     const bool ok = sc >= 0.0f && sc < 4294967296.0f;
@@ -1148,19 +1158,6 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4))) 
         COLD(wave_clk)[2 * wave + 1] = (unsigned long long)wall_clock64();
 }
 
-// Start of a call: counters cleared, and the sub-batches' input / output
-// blocks written from the launch's arguments (a copy from the host would be
-// one more step of the call's chain).
-__global__ void supa_begin(unsigned long long *ctr, Cold *cold, ColdBlocks blocks, int n_cold,
-                           unsigned long long *clk) {
-    for (int q = threadIdx.x; q < CTR_WORDS; q += blockDim.x) ctr[q] = 0ull;
-    if ((int)threadIdx.x < n_cold) cold[threadIdx.x] = blocks.c[threadIdx.x];
-    if (!clk) return;
-    for (int q = threadIdx.x; q < CLK_WORDS; q += blockDim.x) clk[q] = 0ull;
-    __syncthreads();
-    if (threadIdx.x == 0) stamp(clk, CLK_BEGIN);
-}
-
 // the node-log chunks claimed so far, noted for a sub-batch
 __global__ void supa_note_chunks(const unsigned long long *ctr, unsigned long long *sub) {
     if (threadIdx.x == 0) sub[SUB_NCHUNK_END] = ctr[CTR_NCHUNK];
@@ -1186,14 +1183,6 @@ __global__ void supa_azimuth_kernel(const uint32_t *w, int64_t n, float *s, floa
 // ---------------------------------------------------------------------------
 // host-side launchers (called by the C ABI in supa_api.hip)
 // ---------------------------------------------------------------------------
-hipError_t launch_begin(unsigned long long *ctr, Cold *cold, const Cold *h_cold, int n_cold,
-                        unsigned long long *clk, hipStream_t s) {
-    ColdBlocks blocks{};
-    for (int j = 0; j < n_cold; ++j) blocks.c[j] = h_cold[j];
-    hipLaunchKernelGGL(supa_begin, dim3(1), dim3(256), 0, s, ctr, cold, blocks, n_cold, clk);
-    return hipGetLastError();
-}
-
 hipError_t launch_note_chunks(const unsigned long long *ctr, unsigned long long *sub, hipStream_t s) {
     hipLaunchKernelGGL(supa_note_chunks, dim3(1), dim3(64), 0, s, ctr, sub);
     return hipGetLastError();

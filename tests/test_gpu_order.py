@@ -1,0 +1,58 @@
+"""Work order and the first batches dealt out by it: every shower is taken
+exactly once whatever the number of waves, batches and sub-batches, at the
+sizes where the last row of showers ends, and the order itself holds at the
+size where one block stops ordering.  Per-shower results do not depend on the
+order: exact (integers), against the batch order."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2202_05012_amd import supa, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def run(sim, ics, n):
+    ics = [a[:n].contiguous() for a in ics]
+    out = sim.simulate(*ics, 7)
+    return out["counts"].clone(), out["ledger"].clone(), out["total_hits"], out["total_steps"]
+
+
+def ics(n, kind):
+    rng = np.random.default_rng(n)
+    e = {"equal": np.full(n, 3.0), "wide": np.exp(rng.uniform(np.log(0.1), np.log(30), n)),
+         "edge": np.where(rng.random(n) < 0.2, 0.0, rng.uniform(0, 2, n))}[kind]
+    t = lambda a: torch.from_numpy(a.astype(np.float32)).cuda()
+    return t(e), t(rng.uniform(0, 0.5, n)), t(rng.uniform(0, 6, n))
+
+
+@pytest.mark.parametrize("kind", ["equal", "wide", "edge"])
+@pytest.mark.parametrize("subs", [1, 2, 3])
+def test_every_shower_is_taken_once(kind, subs):
+    w = workloads.WORKLOADS["e10_normal_5planes_1k"]
+    geom = workloads.geometry(w)
+    sim = supa.Simulator(geom, supa.OUT_HITS)
+    data = ics(3100, kind)
+    for n in (1, 2, 255, 256, 257, 511, 512, 513, 515, 767, 768, 769, 771, 1023, 1024, 1025, 1027, 2049, 3100):
+        print(f"order: {n} showers, {kind} energies, {subs} sub-batches", flush=True)
+        sim.set_launch(1)                                   # 256 waves
+        sim.set_schedule(subs, 0)
+        a = run(sim, data, n)
+        sim.set_schedule(subs, 1)
+        for _ in range(2):
+            b = run(sim, data, n)
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and a[2:] == b[2:]
+
+
+@pytest.mark.parametrize("n", [4097, 16384, 32767, 32768, 32769, 40000])
+def test_automatic_order(n):
+    """More showers than waves, twelve planes: ordered by default."""
+    print(f"order: {n} showers, automatic", flush=True)
+    w = workloads.WORKLOADS["e10_normal_5planes_1k"]
+    geom = workloads.geometry(w, n_planes=12)
+    data = ics(n, "wide")
+    sim = supa.Simulator(geom, supa.OUT_HITS)
+    auto = run(sim, data, n)
+    sim.set_schedule(1, 0)
+    plain = run(sim, data, n)
+    assert torch.equal(auto[0], plain[0]) and torch.equal(auto[1], plain[1]) and auto[2:] == plain[2:]
