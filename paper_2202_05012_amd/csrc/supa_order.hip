@@ -6,7 +6,7 @@
 // expensive showers first leaves the cheap ones to fill the end of the
 // launch, so no wave starts a long shower when the others are done (longest
 // processing time first).  The order is a counting sort of the showers by
-// a bucket of log2 of their fixed-point energy, descending: three kernels
+// a bucket of the exponent and leading bits of their fixed-point energy, descending: three kernels
 // (histogram, scan of the buckets, scatter), or, up to ORDER_ONE showers, one
 // block of the kernel that starts the call anyway.  The order within a bucket
 // is arbitrary; results do not depend on the order at all.
@@ -23,9 +23,9 @@ constexpr int ORDER_THREADS = 256;
 __device__ __forceinline__ int cost_bucket(float e0, float e_scale) {
     const float v = e0 * e_scale;
     if (!(v >= 1.0f)) return ORDER_BUCKETS - 1;           // tiny, zero, negative or NaN
-    const float l = __log2f(v) * 32.0f;                    // < 32 * 32 for v < 2^32
-    const int b = (int)l;
-    return ORDER_BUCKETS - 1 - min(max(b, 0), ORDER_BUCKETS - 1);
+    // 32 per octave, evenly in the mantissa: exponent and its five leading bits
+    const int b = (int)(__float_as_uint(v) >> 18) - (127 << 5);
+    return ORDER_BUCKETS - 1 - min(b, ORDER_BUCKETS - 1);
 }
 
 __global__ void __launch_bounds__(ORDER_THREADS) order_hist(const float *e0, int n, float e_scale,

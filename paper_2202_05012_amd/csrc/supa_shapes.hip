@@ -956,6 +956,18 @@ __global__ void radius_kernel(int64_t n, const float *x, const float *y, float *
 
 constexpr int W1_THREADS = 256;
 constexpr int W1_HIST_WORDS = 8192;  // LDS histogram words per block (32 KB)
+// Workgroups per sample at most: six per CU, as many as hold their histograms
+// at once; both samples in one launch are two full rounds.  (2,048 per sample
+// and a launch each: the histograms of 100,000 rows of 365 columns 2 x 63 us,
+// a round of two thirds and one of a third; the sums 2 x 40 us.)
+constexpr int W1_BLOCKS = 6 * 256;
+constexpr int W1_ROWS = 8;           // rows per thread and round, all requested before any is used
+
+struct Sample {
+    const float *m;
+    int64_t rows, ld;
+    int rb;                          // row blocks
+};
 
 struct Partial {  // per (row block, column); sums shifted by the column's pivot
     double cnt, s1, s2, mn, mx;
@@ -975,7 +987,7 @@ __host__ __device__ inline int w1_cols_per_tile(int n_cols, int n_bins) {
 __host__ __device__ inline int w1_row_blocks(int64_t rows, int n_cols, int ct) {
     const int64_t tiles = (n_cols + ct - 1) / ct;
     int64_t rb = (rows + 255) / 256;
-    const int64_t cap = 2048 / tiles > 1 ? 2048 / tiles : 1;
+    const int64_t cap = W1_BLOCKS / tiles > 1 ? W1_BLOCKS / tiles : 1;
     if (rb > cap) rb = cap;
     if (rb < 1) rb = 1;
     return (int)rb;
@@ -983,31 +995,36 @@ __host__ __device__ inline int w1_row_blocks(int64_t rows, int n_cols, int ct) {
 
 __device__ inline bool finite(float v) { return __builtin_isfinite(v); }
 
-// grid (tiles, row blocks); one sample per launch.
+// grid (tiles, row blocks of ref, then of smp)
 __global__ void __launch_bounds__(W1_THREADS)
-    w1_stats(const float *m, int64_t rows, int64_t ld, int n_cols, int ct, int rb, Partial *part) {
+    w1_stats(Sample ref, Sample smp, int n_cols, int ct, Partial *part_ref, Partial *part_smp) {
     __shared__ double sh[5][W1_THREADS];
+    const bool first = (int)blockIdx.y < ref.rb;
+    const Sample S = first ? ref : smp;
+    const int block = (int)blockIdx.y - (first ? 0 : ref.rb);
+    Partial *part = first ? part_ref : part_smp;
+    const float *m = S.m;
+    const int64_t rows = S.rows, ld = S.ld;
     const int t = threadIdx.x;
     const int cl = t % ct, ph = t / ct, rpt = W1_THREADS / ct;
     const int c = blockIdx.x * ct + cl;
-    const int64_t per = (rows + rb - 1) / rb;
-    const int64_t r0 = (int64_t)blockIdx.y * per;
+    const int64_t per = (rows + S.rb - 1) / S.rb;
+    const int64_t r0 = (int64_t)block * per;
     const int64_t r1 = r0 + per < rows ? r0 + per : rows;
     double cnt = 0.0, s1 = 0.0, s2 = 0.0;
     float mn = __builtin_inff(), mx = -__builtin_inff();
     if (c < n_cols) {
         const float p0 = m[c];
         const double piv = finite(p0) ? (double)p0 : 0.0;
-        // four rows per round, all requested before any is used
-        for (int64_t r = r0 + ph; r < r1; r += 4 * (int64_t)rpt) {
-            float v[4];
+        for (int64_t r = r0 + ph; r < r1; r += W1_ROWS * (int64_t)rpt) {
+            float v[W1_ROWS];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < W1_ROWS; ++u) {
                 const int64_t q = r + (int64_t)u * rpt;
                 v[u] = q < r1 ? m[q * ld + c] : __builtin_nanf("");
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < W1_ROWS; ++u) {
                 if (!finite(v[u])) continue;
                 const double d = (double)v[u] - piv;
                 cnt += 1.0;
@@ -1033,7 +1050,7 @@ __global__ void __launch_bounds__(W1_THREADS)
             mn = (float)sh[3][u] < mn ? (float)sh[3][u] : mn;
             mx = (float)sh[4][u] > mx ? (float)sh[4][u] : mx;
         }
-        part[(size_t)blockIdx.y * n_cols + c] = Partial{cnt, s1, s2, (double)mn, (double)mx};
+        part[(size_t)block * n_cols + c] = Partial{cnt, s1, s2, (double)mn, (double)mx};
     }
 }
 
@@ -1096,32 +1113,38 @@ __global__ void w1_zero(uint32_t *p, int64_t n) {
         p[i] = 0;
 }
 
-// grid (tiles, row blocks); hist: [n_cols][n_bins] of this sample.
+// grid (tiles, row blocks of ref, then of smp); hist_*: [n_cols][n_bins].
 __global__ void __launch_bounds__(W1_THREADS)
-    w1_hist(const float *m, int64_t rows, int64_t ld, int n_cols, int ct, int rb, int n_bins,
-            const ColInfo *info, uint32_t *hist) {
+    w1_hist(Sample ref, Sample smp, int n_cols, int ct, int n_bins, const ColInfo *info, uint32_t *hist_ref,
+            uint32_t *hist_smp) {
     extern __shared__ uint32_t hb[];  // [ct][n_bins]
+    const bool first = (int)blockIdx.y < ref.rb;
+    const Sample S = first ? ref : smp;
+    const int block = (int)blockIdx.y - (first ? 0 : ref.rb);
+    uint32_t *hist = first ? hist_ref : hist_smp;
+    const float *m = S.m;
+    const int64_t rows = S.rows, ld = S.ld;
     const int t = threadIdx.x;
     for (int i = t; i < ct * n_bins; i += W1_THREADS) hb[i] = 0;
     __syncthreads();
     const int cl = t % ct, ph = t / ct, rpt = W1_THREADS / ct;
     const int c = blockIdx.x * ct + cl;
-    const int64_t per = (rows + rb - 1) / rb;
-    const int64_t r0 = (int64_t)blockIdx.y * per;
+    const int64_t per = (rows + S.rb - 1) / S.rb;
+    const int64_t r0 = (int64_t)block * per;
     const int64_t r1 = r0 + per < rows ? r0 + per : rows;
     if (c < n_cols) {
         const ColInfo ci = info[c];
         if (!ci.skip) {
             uint32_t *h = hb + cl * n_bins;
-            for (int64_t r = r0 + ph; r < r1; r += 4 * (int64_t)rpt) {
-                float v[4];
+            for (int64_t r = r0 + ph; r < r1; r += W1_ROWS * (int64_t)rpt) {
+                float v[W1_ROWS];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < W1_ROWS; ++u) {
                     const int64_t q = r + (int64_t)u * rpt;
                     v[u] = q < r1 ? m[q * ld + c] : __builtin_nanf("");
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < W1_ROWS; ++u) {
                     if (!finite(v[u])) continue;
                     int k = (int)__builtin_floor(((double)v[u] - ci.lo) * ci.scale);
                     k = k < 0 ? 0 : (k >= n_bins ? n_bins - 1 : k);
@@ -1352,17 +1375,13 @@ extern "C" supa_status supa_w1_normalized(void *stream, int32_t n_cols, const fl
 
     const int64_t zero_words = (int64_t)(w.total - w.off_hr) / 4;
     hipLaunchKernelGGL(w1_zero, dim3(cu_count() * 4), dim3(256), 0, s, hr, zero_words);
-    hipLaunchKernelGGL(w1_stats, dim3(w.tiles, w.rbr), dim3(W1_THREADS), 0, s, ref, n_ref, ref_ld,
-                       n_cols, w.ct, w.rbr, pr);
-    hipLaunchKernelGGL(w1_stats, dim3(w.tiles, w.rbs), dim3(W1_THREADS), 0, s, smp, n_smp, smp_ld,
-                       n_cols, w.ct, w.rbs, ps);
+    const Sample A{ref, n_ref, ref_ld, w.rbr}, B{smp, n_smp, smp_ld, w.rbs};
+    hipLaunchKernelGGL(w1_stats, dim3(w.tiles, w.rbr + w.rbs), dim3(W1_THREADS), 0, s, A, B, n_cols, w.ct, pr, ps);
     hipLaunchKernelGGL(w1_colinfo, dim3(n_cols), dim3(WAVE), 0, s, n_cols, n_bins, pr,
                        w.rbr, ps, w.rbs, info);
     const size_t lds = (size_t)w.ct * n_bins * 4;
-    hipLaunchKernelGGL(w1_hist, dim3(w.tiles, w.rbr), dim3(W1_THREADS), lds, s, ref, n_ref, ref_ld,
-                       n_cols, w.ct, w.rbr, n_bins, info, hr);
-    hipLaunchKernelGGL(w1_hist, dim3(w.tiles, w.rbs), dim3(W1_THREADS), lds, s, smp, n_smp, smp_ld,
-                       n_cols, w.ct, w.rbs, n_bins, info, hs);
+    hipLaunchKernelGGL(w1_hist, dim3(w.tiles, w.rbr + w.rbs), dim3(W1_THREADS), lds, s, A, B, n_cols, w.ct, n_bins,
+                       info, hr, hs);
     hipLaunchKernelGGL(w1_distance, dim3(n_cols), dim3(WAVE), 0, s, n_cols, n_bins, info, hr, hs, w1);
     if (group_of_col)
         hipLaunchKernelGGL(w1_groups, dim3(n_groups), dim3(WAVE), 0, s, n_cols, group_of_col,
