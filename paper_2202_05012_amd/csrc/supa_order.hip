@@ -89,13 +89,12 @@ __global__ void order_clear(uint32_t *hist, unsigned long long *clk) {
 // Start of a call: counters cleared, and the sub-batches' input / output
 // blocks written from the launch's arguments (a copy from the host would be
 // one more step of the call's chain).  With ORDER also the work order of its
-// n <= ORDER_ONE showers, by the same block: their buckets in registers, ranks
-// from the LDS counts.
+// n <= ORDER_ONE showers, by the same block: their buckets and ranks in LDS.
 template <bool ORDER>
 __global__ void __launch_bounds__(ORDER ? 1024 : 256)
     supa_begin(unsigned long long *ctr, Cold *cold, ColdBlocks blocks, int n_cold, unsigned long long *clk,
                const float *e0, int n, float e_scale, int32_t *order) {
-    __shared__ uint32_t h[ORDER ? ORDER_BUCKETS : 1], sums[16];
+    __shared__ uint32_t h[ORDER ? ORDER_BUCKETS : 1], sums[16], place[ORDER ? ORDER_ONE : 1];
     const int t = (int)threadIdx.x;
     if (clk) {
         for (int q = t; q < CLK_WORDS; q += blockDim.x)
@@ -106,28 +105,23 @@ __global__ void __launch_bounds__(ORDER ? 1024 : 256)
     for (int q = t; q < CTR_WORDS; q += blockDim.x) ctr[q] = 0ull;
     if (t < n_cold) cold[t] = blocks.c[t];
     if constexpr (ORDER) {
-        constexpr int PER = ORDER_ONE / 1024;
-        static_assert(ORDER_BUCKETS == 1024, "one bucket per thread");
+        static_assert(ORDER_BUCKETS == 1024 && ORDER_ONE <= 1 << 22, "one bucket per thread; rank and bucket in a word");
         h[t] = 0u;
         __syncthreads();
-        int b[PER];
-        uint32_t rank[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) b[q] = t + 1024 * q < n ? cost_bucket(e0[t + 1024 * q], e_scale) : -1;
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
+        // (loops, not straight code run once: its fetch took longer than the work)
+#pragma unroll 2
+        for (int i = t; i < n; i += 1024) {
+            const int b = cost_bucket(e0[i], e_scale);
             // one atomic for the lanes that share the first lane's bucket (all
             // of them in a batch of one energy: 64 in turn on one counter)
-            if (1024 * q >= n) continue;
-            const int b0 = __builtin_amdgcn_readfirstlane(b[q]);
-            const uint64_t same = __ballot(b[q] == b0 && b0 >= 0);
+            const int b0 = __builtin_amdgcn_readfirstlane(b);
+            const uint64_t same = __ballot(b == b0);
+            uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0));
             uint32_t base = 0u;
-            if (same && (t & 63) == 0) base = atomicAdd(&h[b0], (uint32_t)__builtin_popcountll(same));
-            base = __builtin_amdgcn_readfirstlane(base);
-            if (b[q] == b0)
-                rank[q] = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0));
-            else
-                rank[q] = b[q] >= 0 ? atomicAdd(&h[b[q]], 1u) : 0u;
+            if (b != b0 || rank == 0u) base = atomicAdd(&h[b], b != b0 ? 1u : (uint32_t)__builtin_popcountll(same));
+            // (lane of rank 0: the first active one)
+            rank = b == b0 ? rank + __builtin_amdgcn_readfirstlane(base) : base;
+            place[i] = rank << 10 | (uint32_t)b;
         }
         __syncthreads();
         // bucket counts -> starts
@@ -141,12 +135,12 @@ __global__ void __launch_bounds__(ORDER ? 1024 : 256)
         if ((t & 63) == 63) sums[t >> 6] = incl;
         __syncthreads();
         uint32_t before = 0u;
-        for (int w = 0; w < (t >> 6); ++w) before += sums[w];
+#pragma unroll
+        for (int w = 0; w < 16; ++w) before += w < (t >> 6) ? sums[w] : 0u;
         h[t] = before + incl - v;
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (1024 * q < n && b[q] >= 0) order[h[b[q]] + rank[q]] = t + 1024 * q;
+#pragma unroll 2
+        for (int i = t; i < n; i += 1024) order[h[place[i] & 1023u] + (place[i] >> 10)] = i;
     }
     if (!clk) return;
     __syncthreads();
