@@ -52,6 +52,18 @@ __device__ __forceinline__ long long block_excl_scan_ll(long long v, long long *
     return before + incl - v;
 }
 
+// Sum over lanes 0 .. lane by DPP: shifts by 1, 2, 4, 8 within rows of sixteen
+// lanes, then row ends broadcast to the rows above (0 where there is no source).
+__device__ __forceinline__ int32_t wave_scan_add(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
 // tile sums of the hit and node counts
 __global__ void __launch_bounds__(SCAN_THREADS) scan_tiles(ScanParams S) {
     if (S.clk && threadIdx.x == 0 && blockIdx.x == 0) stamp(S.clk, CLK_SCAN);
@@ -137,6 +149,18 @@ __global__ void __launch_bounds__(1024) scan_one(ScanParams S) {
         }
         if (threadIdx.x == 0) S.sub[a == 0 ? SUB_HITS : SUB_NODES] = (unsigned long long)all;
         if (!out) continue;
+        if (sum[a] <= 0x7fffffff) {            // (uniform) the wave's prefix sums fit 32 bits
+            int32_t run = 0;
+#pragma unroll
+            for (int q = 0; q < SCAN_ONE / 1024; ++q) {
+                if (q >= per) break;
+                const int32_t incl = wave_scan_add(v[a][q]);
+                const int64_t i = base + q * 64;
+                if (i < S.n) out[i] = o + run + incl - v[a][q];
+                run += __builtin_amdgcn_readlane(incl, 63);
+            }
+            continue;
+        }
 #pragma unroll
         for (int q = 0; q < SCAN_ONE / 1024; ++q) {
             if (q >= per) break;
