@@ -86,6 +86,21 @@ __global__ void order_clear(uint32_t *hist, unsigned long long *clk) {
     if (q < ORDER_BUCKETS) hist[q] = 0u;
 }
 
+// Rank in bucket b among the showers counted so far (h: the counts), with the
+// bucket in the low ten bits.  One atomic for the lanes that share the first
+// lane's bucket (all of them in a batch of one energy: 64 in turn on one
+// counter).
+__device__ __forceinline__ uint32_t order_rank(uint32_t *h, int b) {
+    const int b0 = __builtin_amdgcn_readfirstlane(b);
+    const uint64_t same = __ballot(b == b0);
+    uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0));
+    uint32_t base = 0u;
+    if (b != b0 || rank == 0u) base = atomicAdd(&h[b], b != b0 ? 1u : (uint32_t)__builtin_popcountll(same));
+    // (lane of rank 0: the first active one)
+    rank = b == b0 ? rank + __builtin_amdgcn_readfirstlane(base) : base;
+    return rank << 10 | (uint32_t)b;
+}
+
 // Start of a call: counters cleared, and the sub-batches' input / output
 // blocks written from the launch's arguments (a copy from the host would be
 // one more step of the call's chain).  With ORDER also the work order of its
@@ -108,20 +123,22 @@ __global__ void __launch_bounds__(ORDER ? 1024 : 256)
         static_assert(ORDER_BUCKETS == 1024 && ORDER_ONE <= 1 << 22, "one bucket per thread; rank and bucket in a word");
         h[t] = 0u;
         __syncthreads();
-        // (loops, not straight code run once: its fetch took longer than the work)
-#pragma unroll 2
-        for (int i = t; i < n; i += 1024) {
-            const int b = cost_bucket(e0[i], e_scale);
-            // one atomic for the lanes that share the first lane's bucket (all
-            // of them in a batch of one energy: 64 in turn on one counter)
-            const int b0 = __builtin_amdgcn_readfirstlane(b);
-            const uint64_t same = __ballot(b == b0);
-            uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0));
-            uint32_t base = 0u;
-            if (b != b0 || rank == 0u) base = atomicAdd(&h[b], b != b0 ? 1u : (uint32_t)__builtin_popcountll(same));
-            // (lane of rank 0: the first active one)
-            rank = b == b0 ? rank + __builtin_amdgcn_readfirstlane(base) : base;
-            place[i] = rank << 10 | (uint32_t)b;
+        // (loops, not straight code run once: its fetch took longer than the
+        // work; the next round's eight loads in flight during a round)
+        float e[8], en[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) e[u] = t + 1024 * u < n ? e0[t + 1024 * u] : 0.0f;
+        for (int i0 = t; i0 - t < n; i0 += 8 * 1024) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) en[u] = i0 + 1024 * (u + 8) < n ? e0[i0 + 1024 * (u + 8)] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + 1024 * u;
+                if (i >= n) continue;
+                place[i] = order_rank(h, cost_bucket(e[u], e_scale));
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) e[u] = en[u];
         }
         __syncthreads();
         // bucket counts -> starts
