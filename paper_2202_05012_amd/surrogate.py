@@ -135,13 +135,15 @@ def features(e0, polar, az, seed, row_base=0, stream_id=0):
     return x
 
 
-def gate(out, e0, n_layers, want_image=False, rho=-1.0, seed=0, row_base=0, y_scale=None):
+def gate(out, e0, n_layers, want_image=False, rho=-1.0, seed=0, row_base=0, y_scale=None, into=None):
     """Per-layer energies (means, or samples when rho >= 0), uncertainty
-    scores and optionally the predicted images; see supa_surrogate.h."""
+    scores and optionally the predicted images; see supa_surrogate.h.
+    into: the tensors for the energies and scores (contiguous rows of larger
+    ones), else new ones."""
     B, D2 = out.shape
     D = D2 // 2
-    layer_e = torch.empty((B, n_layers), dtype=torch.float32, device=out.device)
-    unc = torch.empty(B, dtype=torch.float32, device=out.device)
+    layer_e, unc = into or (torch.empty((B, n_layers), dtype=torch.float32, device=out.device),
+                            torch.empty(B, dtype=torch.float32, device=out.device))
     img = torch.empty((B, D), dtype=torch.float32, device=out.device) if want_image else None
     ys = Y_SCALE if y_scale is None else y_scale
     _check(_lib().supa_surrogate_gate(_stream(), B, D, n_layers, _p(out), _p(e0), ys, S_CLAMP,
