@@ -479,17 +479,20 @@ __global__ void gate_kernel(int B, int D, int L, const float *out, const float *
     if (threadIdx.x == 0) unc[b] = sqrtf(tv) / fmaxf(tm, 1e-6f);
 }
 
-// Per shower b (one wave; lane l < L takes layer l): the per-tile sums of
-// the fused final layer (P[b][tile][2], tiles of GT columns) combined into
+// Per shower b (GL lanes, the power of two from sixteen on that holds the
+// layers: two showers of 20 layers per wave, 27 -> 16 us for 65,536 of them;
+// lane l < L takes layer l): the per-tile sums of the fused final layer (P[b][tile][2], tiles of GT columns) combined into
 // what gate_kernel computes from the full output: per-layer energies (or
 // samples, same Philox counters) and the uncertainty score.
+template <int GL>
 __global__ void __launch_bounds__(256) gate_tiles_kernel(int B, int D, int L, const float *P, const float *e0,
                                                          float y_scale, float *layer_e, float *unc, float rho,
                                                          uint32_t row_base, uint32_t k0, uint32_t k1,
                                                          float *layer_cnt) {
-    const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (b >= B) return;                                   // whole waves leave together
+    const int b0 = blockIdx.x * (256 / GL) + threadIdx.x / GL;
+    const int lane = threadIdx.x % GL;
+    const bool in = b0 < B;
+    const int b = in ? b0 : B - 1;                        // (lanes past the end repeat the last, unwritten)
     const int tiles = 2 * D / GT, tpl = D / L / GT;
     const float *row = P + (int64_t)b * tiles * 2;
     float sm = 0.f, sv = 0.f, ss = 0.f, sc = 0.f;
@@ -500,7 +503,7 @@ __global__ void __launch_bounds__(256) gate_tiles_kernel(int B, int D, int L, co
             sv += row[2 * (D / GT + lane * tpl + t)];
             ss += row[2 * (D / GT + lane * tpl + t) + 1];
         }
-        if (layer_cnt) layer_cnt[(int64_t)b * L + lane] = sc;
+        if (layer_cnt && in) layer_cnt[(int64_t)b * L + lane] = sc;
         float v = sm;
         if (rho >= 0.0f) {
             const uint4 w = philox4x32_10(row_base + (uint32_t)b, (uint32_t)lane, 0x9a7eu, 0u, k0, k1);
@@ -510,15 +513,15 @@ __global__ void __launch_bounds__(256) gate_tiles_kernel(int B, int D, int L, co
             const float z = sqrtf(-2.0f * logf(u1)) * cs;
             v += sqrtf(rho * ss * ss + (1.0f - rho) * sv) * z;
         }
-        layer_e[(int64_t)b * L + lane] = v * (e0[b] / y_scale);
+        if (in) layer_e[(int64_t)b * L + lane] = v * (e0[b] / y_scale);
     }
     float tm = sm, tv = sv;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
+    for (int off = GL / 2; off > 0; off >>= 1) {
         tm += __shfl_xor(tm, off, 64);
         tv += __shfl_xor(tv, off, 64);
     }
-    if (lane == 0) unc[b] = sqrtf(tv) / fmaxf(tm, 1e-6f);
+    if (lane == 0 && in) unc[b] = sqrtf(tv) / fmaxf(tm, 1e-6f);
 }
 
 // y[c][r] = bf16(x[r][c]) (float [rows][cols] -> bf16 [cols][rows])
@@ -1027,8 +1030,14 @@ hipError_t launch_gate_fused(int B, int K, int D, int L, const uint16_t *h, int 
     }
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     if (hipError_t e = mark(2); e != hipSuccess) return e;
-    hipLaunchKernelGGL(gate_tiles_kernel, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, s, B, D, L, partial, e0,
-                       y_scale, layer_e, unc, rho, row_base, (uint32_t)seed, (uint32_t)(seed >> 32), layer_cnt);
+    auto sums = [&](auto kernel, int gl) {
+        const int per = 256 / gl;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((B + per - 1) / per)), dim3(256), 0, s, B, D, L, partial, e0, y_scale,
+                           layer_e, unc, rho, row_base, (uint32_t)seed, (uint32_t)(seed >> 32), layer_cnt);
+    };
+    if (L <= 16) sums(gate_tiles_kernel<16>, 16);
+    else if (L <= 32) sums(gate_tiles_kernel<32>, 32);
+    else sums(gate_tiles_kernel<64>, 64);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     return mark(3);
 }
