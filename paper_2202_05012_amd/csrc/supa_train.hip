@@ -122,6 +122,9 @@ __global__ void __launch_bounds__(256) train_transpose_kernel(TrainArgs a) {
     }
 }
 
+// All waves' LDS accesses are done (their loads and stores to memory need not be).
+__device__ __forceinline__ void meet_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ---------------------------------------------------------------------------
 // Hidden layers forward: 32 rows per workgroup, so that a batch of 8,192 rows
 // covers the 256 CUs; wave w takes outputs 32 w .. + 32 of all rows.  A wave's
@@ -188,7 +191,7 @@ __global__ void __launch_bounds__(512) train_forward_kernel(TrainArgs a) {
             }
         }
         // one barrier per layer: the other buffer was last read before this one's writes
-        __syncthreads();
+        meet_lds();
         if (l + 1 < a.n_hidden) {
 #pragma unroll
             for (int j = 0; j < 2; ++j)
@@ -472,7 +475,10 @@ __global__ void __launch_bounds__(512) train_input_grad_kernel(TrainArgs p) {
 // Hidden layers backward, 32 rows per workgroup (see the forward): g <-
 // (g W^T) GELU' from the last hidden layer's gradient down to the first.
 // Wave w takes inputs 32 w .. + 32; its weight rows [in][out] are contiguous
-// in the reduction as they are stored.
+// in the reduction as they are stored.  The next layer's weights and
+// preactivations are read while this one's are used, and no wave waits for its
+// stores at a barrier (8,192 rows, 3 layers: 34 -> 29.6 us; the forward's
+// barriers without that wait 34 -> 33.3).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(512) train_backward_kernel(TrainArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t X[2][ROWS][PITCH];
@@ -487,14 +493,32 @@ __global__ void __launch_bounds__(512) train_backward_kernel(TrainArgs a) {
             if (m0 + 16 * j < a.B)
                 x[j][kk] = *(const u32x4_t *)(a.g[a.n_hidden - 1] + (int64_t)(m0 + 16 * j) * W + 32 * kk + 8 * lq);
         }
-    for (int l = a.n_hidden - 1; l >= 1; --l) {
-        // gradient of hidden layer l - 1 from that of layer l (weights wb[l])
-        u32x4_t w[2][8];
+    // a layer's weights and preactivations, read while the layer before it is evaluated
+    u32x4_t w[2][8];
+    uint2 pre[2][2];
+    auto read_weights = [&](int l) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk)
                 w[i][kk] = *(const u32x4_t *)(a.wb[l] + (int64_t)(k0 + 16 * i) * W + 32 * kk + 8 * lq);
+    };
+    auto read_pre = [&](int l) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                pre[i][j] = make_uint2(0u, 0u);
+                if (m0 + 16 * j < a.B)
+                    pre[i][j] = *(const uint2 *)(a.pre[l - 1] + (int64_t)(m0 + 16 * j) * W + 32 * wave + 16 * i + 4 * lq);
+            }
+    };
+    if (a.n_hidden > 1) {
+        read_weights(a.n_hidden - 1);
+        read_pre(a.n_hidden - 1);
+    }
+    for (int l = a.n_hidden - 1; l >= 1; --l) {
+        // gradient of hidden layer l - 1 from that of layer l (weights wb[l])
         floatx4_t acc[2][2] = {{kZero4, kZero4}, {kZero4, kZero4}};
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk)
@@ -502,6 +526,7 @@ __global__ void __launch_bounds__(512) train_backward_kernel(TrainArgs a) {
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(w[i][kk], x[j][kk], acc[i][j]);
+        if (l > 1) read_weights(l - 1);
         uint16_t(*Xo)[PITCH] = X[l & 1];
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -510,7 +535,7 @@ __global__ void __launch_bounds__(512) train_backward_kernel(TrainArgs a) {
                 const int m = m0 + 16 * j, f = 32 * wave + 16 * i + 4 * lq;
                 uint2 gv = make_uint2(0u, 0u);
                 if (m < a.B) {
-                    const uint2 pv = *(const uint2 *)(a.pre[l - 1] + (int64_t)m * W + f);
+                    const uint2 pv = pre[i][j];
                     gv = make_uint2(pack2(acc[i][j][0] * gelu_slope(bf_to_f(pv.x & 0xffffu)),
                                           acc[i][j][1] * gelu_slope(bf_to_f(pv.x >> 16))),
                                     pack2(acc[i][j][2] * gelu_slope(bf_to_f(pv.y & 0xffffu)),
@@ -519,8 +544,9 @@ __global__ void __launch_bounds__(512) train_backward_kernel(TrainArgs a) {
                 *(uint2 *)(a.g[l - 1] + (int64_t)m * W + f) = gv;          // (zeros past the batch)
                 *(uint2 *)&Xo[lc + 16 * j][f] = gv;
             }
-        __syncthreads();
         if (l > 1) {
+            read_pre(l - 1);
+            meet_lds();
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
