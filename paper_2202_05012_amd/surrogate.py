@@ -422,8 +422,12 @@ class MLP:
     def _train_bytes(self, x, img):
         """Workspace bytes of the fused training step (supa_mlp_train_step), or
         -1 when it does not take this network or batch: hidden layers of 256,
-        and data it can read 16 bytes at a time."""
+        data it can read 16 bytes at a time, and no part of the step replaced
+        by a subclass."""
         hid = self.dims[1:-1]
+        cls = type(self)
+        if (cls.forward, cls.backward, cls.adam) != (MLP.forward, MLP.backward, MLP.adam):
+            return -1
         tensors = [x, img, *self.W, *self.b, *self.Wb, *self.mW, *self.vW, *self.mb, *self.vb]
         if not hid or any(d != 256 for d in hid) or x.shape[1] != self.dims[0] or x.stride(1) != 1 \
                 or x.stride(0) % 8 or any(t.data_ptr() % 16 for t in tensors):
