@@ -435,8 +435,8 @@ def bench_shapes(args):
     gbs = alg / (k_ms / 1e3) / 1e9
     roof = {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
             "frac": round(gbs / PEAK_HBM_GBS, 4),
-            "traffic": prof_summary.traffic_if_current(prof_dir, "shapes_kernel", wl),
-            "kernel": "shapes_kernel", "kernel_ms": round(k_ms, 4), "alg_bytes": alg}
+            "traffic": prof_summary.traffic_if_current(prof_dir, "shapes_wave_kernel", wl),
+            "kernel": "shapes_wave_kernel", "kernel_ms": round(k_ms, 4), "alg_bytes": alg}
 
     # normalised W1 of every variable, sample 1 against sample 0 (reference)
     mats = [torch.cat([a.view(n, -1), b], dim=1).contiguous() for a, b in ((lv, sv), (lv1, sv1))]

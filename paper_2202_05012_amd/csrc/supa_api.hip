@@ -711,7 +711,7 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
     // much (the planes bound a shower's size); the propagation of 20,000 showers
     // of 1 to 1000 units took 1,600 us in batch order, 683 in this one; of 8,192
     // of 1 to 100 units 194 and 157; at one shower per wave and less it gains
-    // nothing but costs its 4 to 8 us.  The fixed array's layout knows the old
+    // nothing but costs its 2 to 11 us.  The fixed array's layout knows the old
     // limit only, and every sub-batch orders with launches of its own.
     const bool auto_order = n >= kAutoOrderMin || (!fixed && nsub <= 1 && n > L.waves && L.N > 8);
     const bool ordered = c->cost_order > 0 || (c->cost_order < 0 && auto_order);

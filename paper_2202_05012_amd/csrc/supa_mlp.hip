@@ -480,7 +480,7 @@ __global__ void gate_kernel(int B, int D, int L, const float *out, const float *
 }
 
 // Per shower b (GL lanes, the power of two from sixteen on that holds the
-// layers: two showers of 20 layers per wave, 27 -> 16 us for 65,536 of them;
+// layers: two showers of 20 layers per wave, 27 -> 18 us for 65,536 of them;
 // lane l < L takes layer l): the per-tile sums of the fused final layer (P[b][tile][2], tiles of GT columns) combined into
 // what gate_kernel computes from the full output: per-layer energies (or
 // samples, same Philox counters) and the uncertainty score.

@@ -36,6 +36,7 @@ KERNEL_SOURCES = {
     "supa_place": ["supa_place.hip", "supa_device.hpp"],
     "scatter_nodes": ["supa_scatter.hip", "supa_device.hpp"],
     "shapes_kernel": ["supa_shapes.hip"],
+    "shapes_wave_kernel": ["supa_shapes.hip"],
     "w1_stats": ["supa_shapes.hip"],
     "w1_hist": ["supa_shapes.hip"],
     "grids_kernel": ["supa_grids.hip"],
@@ -54,7 +55,7 @@ def source_hash(kernel: str) -> str:
 
 
 def short_name(full: str) -> str:
-    m = re.search(r"(supa_propagate|supa_place|scatter_nodes|scan_tiles|scan_top|scan_apply|shapes_kernel|"
+    m = re.search(r"(supa_propagate|supa_place|scatter_nodes|scan_tiles|scan_top|scan_apply|scan_one|shapes_kernel|shapes_wave_kernel|"
                   r"shapes_clear|w1_stats|w1_hist|w1_colinfo|w1_distance|w1_groups|w1_zero|grids_kernel|"
                   r"gate_fused_k256_kernel|gemm_bf16|gate_tiles_kernel|gate_rows_kernel|features_kernel|mlp_fused_kernel)\b", full)
     return m.group(1) if m else full
