@@ -679,21 +679,28 @@ __device__ inline uint64_t lanes_with(int here, int u) {
     return k <= 0 ? 0ull : k >= WAVE ? ~0ull : (1ull << k) - 1ull;
 }
 
-__device__ inline void add_top(float &e1, float &e2, float o1, float o2) {
+// The two largest of an earlier and a later part's.  As when the hits are taken
+// one by one (run_add): at an energy that is not a number the largest so far
+// becomes the second largest, too.
+__device__ inline void add_top(float &e1, float &e2, float o1, float o2, bool later_nan) {
     e2 = __builtin_fmaxf(__builtin_fmaxf(e2, o2), __builtin_fminf(e1, o1));
+    e2 = later_nan ? __builtin_fmaxf(e2, e1) : e2;
     e1 = __builtin_fmaxf(e1, o1);
 }
 
-// Adds lane - D's pair when it lies in the same row of sixteen and belongs to the same run.
+// Adds lane - D's pair when it lies in the same row of sixteen and belongs to
+// the same run; nan: whether an energy of this lane's part is not a number.
 template <int D>
-__device__ inline void seg_top(float &e1, float &e2, int run) {
+__device__ inline void seg_top(float &e1, float &e2, int &nan, int run) {
     const int r = __builtin_amdgcn_update_dpp(-1, run, 0x110 + D, 0xf, 0xf, false);
     const float o1 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e1), 0x110 + D, 0xf, 0xf, false));
     const float o2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e2), 0x110 + D, 0xf, 0xf, false));
-    float s1 = e1, s2 = e2;
-    add_top(s1, s2, o1, o2);
+    const int on = __builtin_amdgcn_update_dpp(0, nan, 0x110 + D, 0xf, 0xf, false);
+    float s1 = o1, s2 = o2;
+    add_top(s1, s2, e1, e2, nan != 0);
     e1 = r == run ? s1 : e1;
     e2 = r == run ? s2 : e2;
+    nan |= r == run ? on : 0;
 }
 
 // Shape variables of shower s.
@@ -846,10 +853,11 @@ __device__ void wave_shower(const ShapeArgs &A, WaveTile &T, int64_t s, int lane
         T.f.d[11][lane] = acc.ser;
         // the two largest energies of the run's fragments up to this one, in
         // the row of sixteen
-        seg_top<1>(acc.e1, acc.e2, run);
-        seg_top<2>(acc.e1, acc.e2, run);
-        seg_top<4>(acc.e1, acc.e2, run);
-        seg_top<8>(acc.e1, acc.e2, run);
+        int nan_e = acc.se != acc.se ? 1 : 0;
+        seg_top<1>(acc.e1, acc.e2, nan_e, run);
+        seg_top<2>(acc.e1, acc.e2, nan_e, run);
+        seg_top<4>(acc.e1, acc.e2, nan_e, run);
+        seg_top<8>(acc.e1, acc.e2, nan_e, run);
         T.f.top[lane] = f32x2{acc.e1, acc.e2};
         wave_sync();
         // running sums over sixteen fragments, starting anew at each run
@@ -878,14 +886,15 @@ __device__ void wave_shower(const ShapeArgs &A, WaveTile &T, int64_t s, int lane
                 own.sy += T.f.d[2][f];
                 own.syy += T.f.d[3][f];
                 own.sr += T.f.d[4][f];
-                own.se += T.f.d[5][f];
+                const double se = T.f.d[5][f];
+                own.se += se;
                 own.see += T.f.d[6][f];
                 own.sex += T.f.d[7][f];
                 own.sexx += T.f.d[8][f];
                 own.sey += T.f.d[9][f];
                 own.seyy += T.f.d[10][f];
                 own.ser += T.f.d[11][f];
-                add_top(own.e1, own.e2, T.f.top[f].x, T.f.top[f].y);
+                add_top(own.e1, own.e2, T.f.top[f].x, T.f.top[f].y, se != se);
                 f = f == lastf ? WAVE : min(f + 16, lastf);
             }
         }

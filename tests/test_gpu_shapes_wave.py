@@ -89,3 +89,29 @@ def test_segments_at_the_edges(more, hits, L):
     if more:
         assert torch.equal(a.view(torch.int32), a[:1].view(torch.int32).expand_as(a))
         assert torch.equal(b.view(torch.int32), b[:1].view(torch.int32).expand_as(b))
+
+
+def test_energies_that_are_not_numbers():
+    """Both kernels give the same records where energies are NaN or infinite:
+    the energy ratio exactly (no sums), the rest NaN in the same places."""
+    print("shapes: NaN and infinite energies", flush=True)
+    rng = np.random.default_rng(5)
+    L, n, m = 8, 60, 900
+    lay = np.sort(rng.integers(0, L, (n, m)), 1).astype(np.int32)
+    x, y = rng.normal(1, 2, (2, n, m)).astype(np.float32)
+    e = rng.exponential(1, (n, m)).astype(np.float32)
+    e[rng.random((n, m)) < 0.004] = np.nan
+    e[::7][rng.random((len(range(0, n, 7)), m)) < 0.002] = np.inf
+    e[3] = np.nan
+    res = []
+    for more in (0, 17000):                                          # by wave, by lane
+        off = np.concatenate([np.arange(n) * m, np.full(more, n * m)]).astype(np.int64)
+        cnt = np.concatenate([np.full(n, m), np.zeros(more)]).astype(np.int32)
+        lv, sv = SH.shower_shapes(*[_t(v) for v in (off, cnt, x.ravel(), y.ravel(), e.ravel(), lay.ravel())], L)
+        res.append((lv[:n].cpu().numpy(), sv[:n].cpu().numpy()))
+    ratio = SH.LAYER_VARS.index("energy_ratio")
+    np.testing.assert_array_equal(res[0][0][..., ratio], res[1][0][..., ratio])
+    assert np.isnan(res[0][0][..., ratio]).any() and np.isfinite(res[0][0][..., ratio]).any()
+    for a, b in zip(*res):
+        np.testing.assert_array_equal(np.isnan(a), np.isnan(b))
+        np.testing.assert_array_equal(np.isinf(a), np.isinf(b))
