@@ -455,7 +455,7 @@ def bench_shapes(args):
     w1_ms = ev0.elapsed_time(ev1) / args.steps
     w1_bytes = 2 * 2 * n * cols * 4                   # two passes (range, histogram) over both
     tr = [prof_summary.traffic_if_current(prof_dir, k, wl) for k in ("w1_stats", "w1_hist")]
-    w1_traffic = None if None in tr else 2 * (tr[0] + tr[1])   # each kernel runs once per sample
+    w1_traffic = None if None in tr else tr[0] + tr[1]         # one launch of each for both samples
     gm_h = gm.cpu().numpy()
     # the groups of marginals of the paper's performance table (untimed): the
     # per-layer variables grouped across layers, and the point-level marginals
