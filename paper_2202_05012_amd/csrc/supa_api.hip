@@ -669,8 +669,13 @@ static constexpr size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 // context's buffers, grown when needed; otherwise every piece is carved out
 // of the fixed array at `fixed` (kFixedBytes), nothing is allocated, and the
 // pieces are sized to fit it (a batch that needs more fails, see finish).
+// n_layout: the showers the per-shower scratch is laid out for (at least n):
+// the largest of several calls in flight, so that a piece of one call never
+// lies on another piece of its neighbour (each piece is used by one call at a
+// time, but a log start or a scan sum of one call while the next one's order
+// is written).
 static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa_output *out, Plan &L,
-                           int force_nsub, char *fixed = nullptr, int set = 0) {
+                           int force_nsub, char *fixed = nullptr, int set = 0, int64_t n_layout = 0) {
     c->pending.reset();
     const uint32_t outs = c->g.outputs;
     const int64_t n = b->n;
@@ -705,8 +710,9 @@ static supa_status prepare(supa_ctx *c, const supa_batch *b, uint64_t seed, supa
 
     // scratch: per-shower log starts, scan tile sums, work order; per-wave
     // spill; image buckets; hit and node logs
-    const size_t hstart_b = L.recs ? al256((size_t)n * 8) : 0;
-    const size_t part_b = al256((size_t)supa::scan_partial_words(n) * 8);
+    const int64_t n_lay = std::max(n, n_layout);
+    const size_t hstart_b = L.recs ? al256((size_t)n_lay * 8) : 0;
+    const size_t part_b = al256((size_t)supa::scan_partial_words(n_lay) * 8);
     // Automatic work order: when showers have to wait for a wave, and can differ
     // much (the planes bound a shower's size); the propagation of 20,000 showers
     // of 1 to 1000 units took 1,600 us in batch order, 683 in this one; of 8,192
@@ -1277,7 +1283,11 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
     }
     if (k == 0) return SUPA_OK;
     HIP_TRY(c, hipSetDevice(c->device));
-    for (int32_t j = 0; j < k; ++j) size_logs(c, &b[j], &out[j]);
+    int64_t n_layout = 0;
+    for (int32_t j = 0; j < k; ++j) {
+        size_logs(c, &b[j], &out[j]);
+        n_layout = std::max(n_layout, b[j].n);
+    }
     // pinned per-call staging, device per-call blocks, counters and events
     size_t calls_n = c->h_calls_n;
     if (!ensure_pinned((void **)&c->h_calls, &calls_n, (size_t)k * sizeof(supa::Cold)))
@@ -1314,7 +1324,7 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
         supa_status st = SUPA_OK;
         for (int pass = 0; pass < 2 && st == SUPA_OK; ++pass)
             for (int32_t j = 0; j < k && st == SUPA_OK; ++j) {
-                st = prepare(c, &b[j], seed, &out[j], plans[j], 1, nullptr, j & 1);
+                st = prepare(c, &b[j], seed, &out[j], plans[j], 1, nullptr, j & 1, n_layout);
                 if (pass == 1) c->h_calls[j] = c->h_cold[0];
             }
         if (st != SUPA_OK) return st;

@@ -56,3 +56,47 @@ def test_automatic_order(n):
     sim.set_schedule(1, 0)
     plain = run(sim, data, n)
     assert torch.equal(auto[0], plain[0]) and torch.equal(auto[1], plain[1]) and auto[2:] == plain[2:]
+
+
+def test_captured_call_orders_at_each_replay():
+    """5,000 showers of twelve planes: the work order is part of the captured
+    call and follows the energies the input holds at the replay."""
+    w = workloads.WORKLOADS["e10_normal_5planes_1k"]
+    geom = workloads.geometry(w, n_planes=12)
+    n = 5000
+    a, b = ics(n, "wide"), ics(n, "edge")
+    sim = supa.Simulator(geom, supa.OUT_HITS)
+    eager = [run(sim, d, n) for d in (a, b)]
+    args = [t.clone() for t in a]
+    out = sim.allocate(n, 1 << 22)
+    assert sim.run(*args, 7, out) == 0
+    g = sim.graph(*args, 7, out)
+    for rep, d in enumerate((a, b, a)):
+        print(f"order: replay {rep}", flush=True)
+        for t, s in zip(args, d):
+            t.copy_(s)
+        out["counts"].fill_(-1)
+        g.launch()
+        g.check()
+        torch.cuda.synchronize()
+        ref = eager[rep % 2]
+        assert torch.equal(out["counts"], ref[0]) and torch.equal(out["ledger"], ref[1])
+        assert out["total_hits"] == ref[2]
+    g.close()
+
+
+def test_pipelined_calls_with_a_work_order():
+    """Calls of 5,000, 4,097 and 6,000 showers, each ordered, in one entry."""
+    print("order: three calls in one", flush=True)
+    w = workloads.WORKLOADS["e10_normal_5planes_1k"]
+    geom = workloads.geometry(w, n_planes=12)
+    sizes = [5000, 4097, 6000]
+    data = ics(sum(sizes), "wide")
+    sim = supa.Simulator(geom, supa.OUT_HITS)
+    calls = [(sum(sizes[:j]), m) for j, m in enumerate(sizes)]
+    outs = [sim.allocate(m, 1 << 21) for m in sizes]
+    assert sim.run_batches(*data, 7, calls, outs) == 0
+    for (s0, m), o in zip(calls, outs):
+        ref = sim.simulate(*[t[s0:s0 + m].contiguous() for t in data], 7, shower_id_base=s0)
+        assert torch.equal(o["counts"], ref["counts"]) and torch.equal(o["ledger"], ref["ledger"])
+        assert torch.equal(o["hit_offsets"], ref["hit_offsets"]) and o["total_hits"] == ref["total_hits"]
