@@ -13,6 +13,7 @@
 #include <cstring>
 #include <mutex>
 #include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -1188,7 +1189,10 @@ extern "C" supa_status supa_simulate(supa_ctx *c, const supa_batch *b, uint64_t 
         st = run_once(c, b, out, L);
         if (st != SUPA_OK) return st;
         const int r = finish(c, L, out);
-        if (r == SUPA_ERR_CAPACITY) c->pending = std::make_shared<Plan>(L);
+        if (r == SUPA_ERR_CAPACITY) {
+            Plan *p = new (std::nothrow) Plan(L);   // (none: the caller repeats the call)
+            if (p) c->pending.reset(p);
+        }
         if (r >= 0) return (supa_status)r;
     }
     return fail(c, SUPA_ERR_NOMEM, "scratch sizes did not converge");
