@@ -1259,7 +1259,7 @@ extern "C" supa_status supa_simulate_noalloc(supa_ctx *c, const supa_batch *b, u
 // come in two sets, used by alternate calls; a call reuses a set once the
 // second stream is done with the call before the previous one.  Each call's
 // counters are copied aside when its second-stream work ends and read back
-// together with one synchronisation at the end.
+// together with one synchronisation at the end.  Empty calls launch nothing.
 // ---------------------------------------------------------------------------
 static bool ensure_pinned(void **p, size_t *have, size_t need) {
     if (need <= *have) return true;
@@ -1328,6 +1328,7 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
         supa_status st = SUPA_OK;
         for (int pass = 0; pass < 2 && st == SUPA_OK; ++pass)
             for (int32_t j = 0; j < k && st == SUPA_OK; ++j) {
+                if (b[j].n == 0) continue;
                 st = prepare(c, &b[j], seed, &out[j], plans[j], 1, nullptr, j & 1, n_layout);
                 if (pass == 1) c->h_calls[j] = c->h_cold[0];
             }
@@ -1337,10 +1338,12 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
         HIP_TRY(c, hipMemcpyAsync(d_calls, c->h_calls, (size_t)k * sizeof(supa::Cold), hipMemcpyHostToDevice,
                                   c->stream));
         unsigned long long *snap = (unsigned long long *)c->snap.p;
+        bool used[2] = {false, false};
         for (int32_t j = 0; j < k; ++j) {
             const int q = j & 1;
-            // the set's buffers are free once the second stream is done with call j - 2
-            if (j >= 2) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_set_free[q], 0));
+            if (b[j].n == 0) continue;
+            // the set's buffers are free once the second stream is done with the call before on it
+            if (used[q]) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_set_free[q], 0));
             hipEvent_t *e = &c->call_ev[(size_t)j * 5];
             hipEvent_t ev_prop[1][2] = {{e[0], e[1]}}, ev_post[1][2] = {{e[2], e[4]}}, ev_place[1] = {e[3]};
             st = enqueue(c, &b[j], &out[j], plans[j], d_calls + j, nullptr, nullptr, nullptr, c->stream, c->aux, true, ev_prop, ev_post,
@@ -1352,6 +1355,7 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
                                       supa::CTR_WORDS * sizeof(unsigned long long), hipMemcpyDeviceToDevice,
                                       c->aux));
             HIP_TRY(c, hipEventRecord(c->ev_set_free[q], c->aux));
+            used[q] = true;
         }
         HIP_TRY(c, hipEventRecord(c->ev_joined, c->aux));
         HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_joined, 0));
@@ -1360,6 +1364,7 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         float t_prop = 0, t_post = 0, t_all = 0, t_place = 0, t_scatter = 0, t = 0;
         for (int32_t j = 0; j < k; ++j) {
+            if (b[j].n == 0) continue;
             const hipEvent_t *e = &c->call_ev[(size_t)j * 5];
             if (hipEventElapsedTime(&t, e[0], e[1]) == hipSuccess) t_prop += t;
             const hipEvent_t ev_post[2] = {e[2], e[4]};
@@ -1379,6 +1384,7 @@ extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_
         bool rerun = false, cap = false;
         int first_cap = -1;
         for (int32_t j = 0; j < k; ++j) {
+            if (b[j].n == 0) continue;           // (check_call has set its totals to 0)
             const int r = finish(c, plans[j], &out[j], false, c->h_snap + (size_t)j * supa::CTR_WORDS);
             if (r < 0) {
                 rerun = true;

@@ -100,3 +100,21 @@ def test_pipelined_calls_with_a_work_order():
         ref = sim.simulate(*[t[s0:s0 + m].contiguous() for t in data], 7, shower_id_base=s0)
         assert torch.equal(o["counts"], ref["counts"]) and torch.equal(o["ledger"], ref["ledger"])
         assert torch.equal(o["hit_offsets"], ref["hit_offsets"]) and o["total_hits"] == ref["total_hits"]
+
+
+@pytest.mark.parametrize("sizes", [[0, 0], [0, 700, 0], [300, 0, 500, 0, 0, 40, 600]])
+def test_pipelined_calls_some_of_them_empty(sizes):
+    """Calls without showers between others: nothing to do, totals of zero."""
+    print(f"order: calls of {sizes} showers in one", flush=True)
+    w = workloads.WORKLOADS["e10_normal_5planes_1k"]
+    sim = supa.Simulator(workloads.geometry(w), supa.OUT_HITS)
+    data = ics(max(1, sum(sizes)), "wide")
+    calls = [(sum(sizes[:j]), m) for j, m in enumerate(sizes)]
+    outs = [sim.allocate(m, 1 << 18) for m in sizes]
+    for _ in range(2):
+        assert sim.run_batches(*data, 7, calls, outs) == 0
+        for (s0, m), o in zip(calls, outs):
+            ref = sim.simulate(*[t[s0:s0 + m].contiguous() for t in data], 7, shower_id_base=s0)
+            assert torch.equal(o["counts"], ref["counts"]) and torch.equal(o["ledger"], ref["ledger"])
+            assert all(o[k] == ref[k] for k in ("total_hits", "total_nodes", "total_steps"))
+            assert m > 0 or o["total_steps"] == 0
