@@ -243,7 +243,8 @@ supa_status supa_simulate(supa_ctx *ctx, const supa_batch *b, uint64_t seed,
  * in that call (ledger, counts, offsets and images unchanged: the same
  * memory), but for the record arrays and their capacities.  Returns OK,
  * CAPACITY (still too small: may be called again), INVALID_ARG, or STATE when
- * there is no such call.
+ * there is no such call: another one was made since, also an empty one or one
+ * that was refused, or the last one was given other arrays than `out`.
  */
 supa_status supa_place_again(supa_ctx *ctx, supa_output *out);
 

@@ -639,6 +639,7 @@ static supa_status check_call(supa_ctx *c, const supa_batch *b, supa_output *out
     if (!c) return SUPA_ERR_STATE;
     if (c->broken) return fail(c, SUPA_ERR_STATE, "context unusable after a device error");
     c->err.clear();
+    c->pending.reset();                  // (whatever comes of this call)
     std::string why;
     const supa_status s = check_args(c->g.outputs, b, out, why);
     if (s != SUPA_OK) return fail(c, s, why);
@@ -649,6 +650,7 @@ static supa_status check_call(supa_ctx *c, const supa_batch *b, supa_output *out
 // Everything one call launches: parameters and scratch pointers.
 struct Plan {
     const float *e0;                 // (never read here)
+    supa_output given;               // the caller's arrays (of a pending call)
     bool tree, hits_out, images, recs, post;
     int N, nsub, phases;
     int64_t n, waves, img_words;     // waves: what the scratch is sized for
@@ -1191,7 +1193,10 @@ extern "C" supa_status supa_simulate(supa_ctx *c, const supa_batch *b, uint64_t 
         const int r = finish(c, L, out);
         if (r == SUPA_ERR_CAPACITY) {
             Plan *p = new (std::nothrow) Plan(L);   // (none: the caller repeats the call)
-            if (p) c->pending.reset(p);
+            if (p) {
+                p->given = *out;
+                c->pending.reset(p);
+            }
         }
         if (r >= 0) return (supa_status)r;
     }
@@ -1208,15 +1213,28 @@ extern "C" supa_status supa_place_again(supa_ctx *c, supa_output *out) {
     supa_batch b{};
     b.e0 = b.polar = b.azimuth = L.e0;
     b.n = L.n;
+    if (!out) return fail(c, SUPA_ERR_INVALID_ARG, "output is NULL");
+    // the counts and offsets that the placement goes by are in the caller's
+    // arrays: with others this is another call than the pending one (whose
+    // caller may still come)
+    const supa_output &g = L.given;
+    const bool mine = out->ledger == g.ledger && out->counts == g.counts &&
+                      (!L.hits_out || out->hit_offsets == g.hit_offsets) &&
+                      (!L.tree || out->node_offsets == g.node_offsets) && (!L.images || out->images == g.images);
+    const char *other = "the last call on this context was made with other arrays";
     std::string why;
     const supa_status v = check_args(c->g.outputs, &b, out, why);
-    if (v != SUPA_OK) return fail(c, v, why);
-    if (L.place_keys != (L.hits_out && (c->g.outputs & SUPA_OUT_KEYS) && out->hit_key != nullptr))
+    if (v != SUPA_OK) return mine ? fail(c, v, why) : fail(c, SUPA_ERR_STATE, other);
+    if (mine && L.place_keys != (L.hits_out && (c->g.outputs & SUPA_OUT_KEYS) && out->hit_key != nullptr))
         return fail(c, SUPA_ERR_INVALID_ARG, "hit_key given to one of the two calls only");
     HIP_TRY(c, hipSetDevice(c->device));
     out->total_hits = out->total_nodes = out->total_steps = 0;
     const int r = finish(c, L, out);
     if (r != SUPA_OK) return (supa_status)r;
+    if (!mine) {
+        out->total_hits = out->total_nodes = out->total_steps = 0;
+        return fail(c, SUPA_ERR_STATE, other);
+    }
     const bool timed = !c->stamped;
     float post = 0, place = 0, scatter = 0;
     for (int j = 0; j < L.nsub; ++j) {
@@ -1277,6 +1295,7 @@ static bool ensure_pinned(void **p, size_t *have, size_t need) {
 extern "C" supa_status supa_simulate_batches(supa_ctx *c, int32_t k, const supa_batch *b, uint64_t seed,
                                              supa_output *out) {
     if (!c) return SUPA_ERR_STATE;
+    c->pending.reset();
     if (k < 0 || (k > 0 && (!b || !out))) return fail(c, SUPA_ERR_INVALID_ARG, "bad call list");
     for (int32_t j = 0; j < k; ++j) {
         const supa_status st = check_call(c, &b[j], &out[j]);

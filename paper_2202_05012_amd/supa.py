@@ -488,7 +488,7 @@ class Simulator:
             _, o = self._marshal(e0, polar, azimuth, out, x0, y0, shower_id_base)
             st = self.lib.supa_place_again(self.ctx, C.byref(o))
             self._totals(out, o)
-            if st == 5:                    # another call on this context came between
+            if st in (3, 5):               # another call on this context came between
                 st = self.run(e0, polar, azimuth, seed, out, x0, y0, shower_id_base)
             self._check(st)
         th, tn = out["total_hits"], out["total_nodes"]

@@ -73,3 +73,64 @@ def test_nothing_to_place_again():
     for k in ("hit_x", "hit_y", "hit_e"):
         assert torch.equal(out[k][:total].sort()[0], ref[k].sort()[0])
     assert torch.equal(out["hit_offsets"], ref["hit_offsets"])
+
+
+class Interrupted(supa.Simulator):
+    """Another call on the context between a call and its placement again."""
+    between = None
+
+    def allocate(self, n, *room):
+        if n == 0 and self.between:
+            call, self.between = self.between, None
+            call(self)
+        return super().allocate(n, *room)
+
+
+# the other call: fewer or more showers, enough room or not, none at all, refused
+@pytest.mark.parametrize("other,room,status", [(20, 4, 3), (900, 4, 3), (900, 1 << 22, 0), (0, 4, 0), (50, 4, 1)])
+@pytest.mark.parametrize("outputs", [H | K, H | I | K | T])
+def test_another_call_between(other, room, status, outputs):
+    print(f"placed again: {other} showers between, room {room}, outputs {outputs}", flush=True)
+    w = workloads.WORKLOADS["e1to100_20planes_img32_100k"]
+    geom = workloads.geometry(w)
+    (_, dev), (_, dev2) = ics(w, 200), ics(w, max(1, other))
+    dev2 = [t[:other].contiguous() for t in dev2]
+    sim = Interrupted(geom, outputs)
+    outs = Interrupted.allocate(sim, max(1, other), room, room)
+
+    def call(sim):
+        b, o = sim._marshal(*dev2, outs, None, None, 0)
+        if status == 1:                                      # refused: more showers than the arrays hold
+            o.shower_capacity = other - 1
+        assert sim.lib.supa_simulate(sim.ctx, C.byref(b), 5, C.byref(o)) == status
+    sim.between = call
+    out = sim.simulate(*dev, w.seed, hit_capacity=4, node_capacity=4)
+    assert sim.between is None
+    ref = sim.simulate(*dev, w.seed, hit_capacity=1 << 20, node_capacity=1 << 20)
+    parity.check_same_outputs(out, ref)
+
+
+def test_other_arrays_and_later_calls_are_refused():
+    w = workloads.WORKLOADS["e10_normal_5planes_1k"]
+    _, dev = ics(w, 100)
+    sim = supa.Simulator(workloads.geometry(w), H)
+    lib = sim.lib
+
+    def again(out):
+        _, o = sim._marshal(*dev, out, None, None, 0)
+        return lib.supa_place_again(sim.ctx, C.byref(o))
+
+    small, big = sim.allocate(100, 4), sim.allocate(100, 1 << 16)
+    rows = ("ledger", "counts", "hit_offsets")
+    for k in rows:                                           # one array of another call each
+        assert sim.run(*dev, 1, small) == 3
+        assert again(dict(big, **{r: small[r] for r in rows if r != k})) == 5
+        assert again(dict(big, **{r: small[r] for r in rows})) == 0     # the call itself may still come
+    none = [t[:0].contiguous() for t in dev]
+    for later in (lambda: sim.run(*none, 1, small),
+                  lambda: sim.run_batches(*dev, 1, [], []),
+                  lambda: sim.run_batches(*dev, 1, [(0, 0)], [small]),
+                  lambda: sim.run_noalloc(*none, 1, small)):
+        assert sim.run(*dev, 1, small) == 3
+        later()
+        assert again(dict(big, **{r: small[r] for r in rows})) == 5
