@@ -3,6 +3,7 @@ logs, are placed again into larger ones.  Against the oracle (as a call with
 enough room), for every kind of record, with items, sub-batches and a work
 order; and the cases with nothing to place again."""
 import ctypes as C
+import time
 
 import numpy as np
 import pytest
@@ -134,3 +135,24 @@ def test_other_arrays_and_later_calls_are_refused():
         assert sim.run(*dev, 1, small) == 3
         later()
         assert again(dict(big, **{r: small[r] for r in rows})) == 5
+
+
+# too few of both (nothing is placed by the call itself), of hits, of nodes; events instead of stamps
+@pytest.mark.parametrize("room,subs", [((4, 4), 1), ((4, 1 << 22), 1), ((1 << 22, 4), 1), ((4, 4), 2)])
+def test_times_leave_out_the_host_between(room, subs):
+    w = workloads.WORKLOADS["e1to100_20planes_img32_100k"]
+    _, dev = ics(w, 300)
+    sim = supa.Simulator(workloads.geometry(w), H | K | T)
+    sim.set_schedule(subs, 0)
+    assert sim.run(*dev, 1, sim.allocate(300, 1 << 22, 1 << 22)) == 0      # (scratch has its size)
+    small = sim.allocate(300, *room)
+    assert sim.run(*dev, 1, small) == 3
+    time.sleep(0.5)
+    out = dict(sim.allocate(0, 1 << 22, 1 << 22),
+               **{k: small[k] for k in ("ledger", "counts", "hit_offsets", "node_offsets")})
+    _, o = sim._marshal(*dev, out, None, None, 0)
+    assert sim.lib.supa_place_again(sim.ctx, C.byref(o)) == 0
+    ms = sim.timing()
+    print(f"placed again: times {ms}", flush=True)
+    assert ms[3] > 0 and ms[4] > 0 and ms[0] > 0
+    assert ms[0] + ms[1] <= 1.001 * ms[2] + 1e-3 < 100.0
