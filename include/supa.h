@@ -420,7 +420,8 @@ supa_status supa_graph_destroy(supa_graph *graph);
  * [0] propagation kernels (summed over sub-batches), [1] placement
  * of hits, images and nodes (summed; with sub-batches they overlap [0]),
  * [2] whole call (including work ordering and segment offsets).  Host
- * pointer to 3 floats.
+ * pointer to 3 floats.  Waits for no other work, and may be called while a
+ * stream is being captured.
  */
 supa_status supa_last_timing(const supa_ctx *ctx, float *ms3);
 

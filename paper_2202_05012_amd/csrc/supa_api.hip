@@ -127,6 +127,7 @@ struct supa_ctx {
     unsigned long long *d_ctr = nullptr;
     unsigned long long *h_ctr = nullptr;   // pinned
     unsigned long long *d_clk = nullptr;   // time stamps of a call's kernels (behind d_ctr)
+    unsigned long long *h_clk = nullptr;   // their pinned host copy (behind h_ctr)
     supa::Cold *d_cold = nullptr;          // per-sub-batch inputs/outputs blocks (device)
     supa::Cold *h_cold = nullptr;          // their pinned host staging copy
     // launch settings and scratch
@@ -383,15 +384,16 @@ extern "C" supa_status supa_init_geometry(const supa_geometry *g, int device, vo
                         hipMemcpyHostToDevice) == hipSuccess &&
               hipMalloc(&c->d_c2, THR_ENTRIES * sizeof(uint64_t)) == hipSuccess &&
               hipMalloc(&c->d_ctr, (2 * supa::CTR_WORDS + supa::CLK_WORDS) * sizeof(unsigned long long)) == hipSuccess &&
-              hipHostMalloc(&c->h_ctr, supa::CTR_WORDS * sizeof(unsigned long long), 0) == hipSuccess &&
+              hipHostMalloc(&c->h_ctr, (supa::CTR_WORDS + supa::CLK_WORDS) * sizeof(unsigned long long), 0) == hipSuccess &&
               hipMalloc(&c->d_cold, supa::MAX_SUB * sizeof(supa::Cold)) == hipSuccess &&
               hipMalloc(&c->d_wclk, (size_t)2 * 32 * c->n_cu * sizeof(unsigned long long)) == hipSuccess &&
               hipHostMalloc(&c->h_cold, supa::MAX_SUB * sizeof(supa::Cold), 0) == hipSuccess &&
               hipMemcpy(c->d_layer, c->layer.data(), N * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(c->d_c1, c1.data(), THR_ENTRIES * sizeof(uint64_t), hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(c->d_c2, c2.data(), THR_ENTRIES * sizeof(uint64_t), hipMemcpyHostToDevice) == hipSuccess;
-    // default priority, and no implicit synchronisation with the null stream
     c->d_clk = ok ? c->d_ctr + 2 * supa::CTR_WORDS : nullptr;
+    c->h_clk = ok ? c->h_ctr + supa::CTR_WORDS : nullptr;
+    // default priority, and no implicit synchronisation with the null stream
     ok = ok && hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) == hipSuccess;
     for (hipEvent_t *e : {&c->ev_begin, &c->ev_end, &c->ev_joined})
         ok = ok && hipEventCreate(e) == hipSuccess;
@@ -497,19 +499,30 @@ extern "C" supa_status supa_last_subtrees(const supa_ctx *c, int64_t *counts5) {
     return SUPA_OK;
 }
 
-// Times of a call whose kernels stamped the clock (after its end).
+// Times of a call whose kernels stamped the clock (after its end).  A query
+// like any other: it waits for nothing but its own copy (on the context's own
+// stream), is allowed while a stream is being captured, and leaves the thread's
+// device as it was.
 static void resolve_timing(const supa_ctx *c) {
     if (!c->stamped) return;
     c->stamped = false;
-    int rate_khz = 0;
-    unsigned long long h[supa::CLK_WORDS];
-    if (hipSetDevice(c->device) != hipSuccess ||
-        hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, c->device) != hipSuccess || rate_khz <= 0 ||
-        hipMemcpy(h, c->d_clk, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess) {
-        (void)hipGetLastError();
+    int rate_khz = 0, device = -1;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const bool got = hipGetDevice(&device) == hipSuccess && hipSetDevice(c->device) == hipSuccess &&
+                     hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, c->device) == hipSuccess &&
+                     rate_khz > 0 &&
+                     hipMemcpyAsync(c->h_clk, c->d_clk, supa::CLK_WORDS * sizeof(unsigned long long),
+                                    hipMemcpyDeviceToHost, c->aux) == hipSuccess &&
+                     hipStreamSynchronize(c->aux) == hipSuccess;
+    if (!got) (void)hipGetLastError();
+    if (device >= 0 && device != c->device) (void)hipSetDevice(device);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!got) {
         std::fill(c->timing, c->timing + 5, 0.0f);
         return;
     }
+    const unsigned long long *h = c->h_clk;
     const unsigned long long begin = h[supa::CLK_BEGIN], scan = h[supa::CLK_SCAN];
     unsigned long long first[2] = {~0ull, ~0ull}, last[2] = {0, 0};
     for (int a = 0; a < 2; ++a)
