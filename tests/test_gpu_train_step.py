@@ -82,3 +82,35 @@ def test_unaligned_and_odd_networks_take_the_general_path():
     with pytest.raises(Exception):
         net.train_step(x[:60], img[:60], e0[:60])             # 60 rows: not a multiple of 8
     assert net.step == 1
+
+
+@pytest.mark.parametrize("part", ["forward", "backward", "adam"])
+@pytest.mark.parametrize("how", ["subclass", "class", "network", "other network"])
+def test_replaced_parts_of_the_step_are_called(part, how, monkeypatch):
+    """A part replaced on a subclass, on the class, on the network or by another
+    network's method is what the step calls, as when it goes layer by layer."""
+    x, img, e0 = data(64, 32, 20, 1)
+    called = []
+    plain = getattr(S.MLP, part)
+
+    def replaced(self, *args, **kw):
+        called.append(part)
+        return plain(self, *args, **kw)
+    cls = type("Sub", (S.MLP,), {part: replaced}) if how == "subclass" else S.MLP
+    net, other = cls([32, 256, 40], seed=1), S.MLP([32, 256, 40], seed=1)
+    if how == "class":
+        monkeypatch.setattr(S.MLP, part, replaced)
+    elif how == "network":
+        setattr(net, part, lambda *args, **kw: replaced(net, *args, **kw))
+    elif how == "other network":
+        setattr(net, part, getattr(other, part))
+        before = [w.clone() for w in (*net.W, *other.W)]
+    net.train_step(x, img, e0)
+    if how != "other network":
+        assert called == [part]
+    elif part == "adam":                                      # the other network is the one that is stepped
+        assert (net.step, other.step) == (0, 1)
+        assert [torch.equal(a, b) for a, b in zip(before, (*net.W, *other.W))] == [True, True, False, False]
+    else:
+        assert (net.step, other.step) == (1, 0)
+    assert net._train_bytes(x, img) < 0
