@@ -401,6 +401,8 @@ extern "C" supa_status supa_mlp_train_step(void *stream, int B, int k_in, int n_
         return bad("need 1..8 hidden layers of 256, inputs a multiple of 16 up to 256, rows and outputs multiples of 8");
     if (!x || !img || !e0 || !weights || !bias || !weights_bf16 || !moments || !loss || !work) return bad("NULL argument");
     if (ldx < k_in || ldx % 8) return bad("bad leading dimension");
+    if (!(s_clamp >= 0) || !std::isfinite(s_clamp)) return bad("s_clamp must be finite and >= 0");
+    if (mse_mean != 0 && mse_mean != 1) return bad("mse_mean must be 0 or 1");
     if (step < 1) return bad("step counts from 1");
     auto off16 = [](const void *p) { return p == nullptr || ((uintptr_t)p & 15) != 0; };
     supa::TrainArgs a{};

@@ -228,3 +228,22 @@ def test_judge_entry_points_reject_bad_arguments_on_the_host():
     assert L.supa_sort_columns(None, 100, 3, fake, 2, fake, fake, 1 << 20) == 1       # ld < cols
     assert L.supa_sort_columns(None, 0, 3, fake, 3, fake, fake, 0) == 0              # empty: nothing to do
     assert L.supa_occupied_counts(None, 10, 0, 16, fake, 0.1, fake) == 1
+
+
+def test_train_step_rejects_what_the_loss_rejects():
+    import ctypes as C
+    from paper_2202_05012_amd import surrogate as S
+    L = S._lib()
+    fake = C.c_void_p(4096)                       # never dereferenced: rejected first
+    ptrs = (C.c_void_p * 8)(*[4096] * 8)
+    need = L.supa_mlp_train_workspace_bytes(64, 32, 1, 40)
+    assert need > 0
+    step = lambda s_clamp, mse: L.supa_mlp_train_step(None, 64, 32, 1, 40, fake, 32, fake, fake, 1.0, s_clamp, mse, ptrs,
+                                                      ptrs, ptrs, ptrs, 1e-3, 0.9, 0.999, 1e-8, 1, fake, fake, need)
+    loss = lambda s_clamp, mse: L.supa_nll_grad(None, 64, 20, fake, fake, fake, 1.0, s_clamp, mse, fake, fake)
+    for call in (loss, step):
+        for s_clamp in (-1.0, -1e-30, float("inf"), float("nan")):
+            assert call(s_clamp, 1) == 1
+            assert "s_clamp" in L.supa_surrogate_last_error().decode()
+        assert call(20.0, 2) == 1
+        assert "mse_mean" in L.supa_surrogate_last_error().decode()
