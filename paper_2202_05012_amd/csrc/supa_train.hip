@@ -285,10 +285,12 @@ __device__ __forceinline__ float ft_loss(const TrainArgs &a, int t, const FtTile
                 const float sr = lv[i][j][q] + bs[q];
                 const float s = __builtin_amdgcn_fmed3f(sr, -a.s_clamp, a.s_clamp);
                 // (y_scale img) / e0 correctly rounded, from the rounded
-                // reciprocal (Markstein's two fused steps)
+                // reciprocal (Markstein's two fused steps; an e0 or target
+                // that is zero, infinite or no number as in a division)
                 const float yn = y[i][j][q] * a.y_scale;
                 const float y0 = yn * ie0[j];
-                const float r = fmaf(fmaf(-y0, e0[j], yn), ie0[j], y0) - (mu[i][j][q] + bm[q]);
+                const float yq = __builtin_amdgcn_div_fixupf(fmaf(fmaf(-y0, e0[j], yn), ie0[j], y0), e0[j], yn);
+                const float r = yq - (mu[i][j][q] + bm[q]);
                 const float ie = __expf(-s);
                 const float e2 = r * r * ie;
                 lj += 0.5f * (s + e2);

@@ -114,3 +114,27 @@ def test_replaced_parts_of_the_step_are_called(part, how, monkeypatch):
     else:
         assert (net.step, other.step) == (1, 0)
     assert net._train_bytes(x, img) < 0
+
+
+# (rows 3 and 60 of e0; bins of rows 5 and 61 of img), each a valid float of no use as an energy
+@pytest.mark.parametrize("e", [None, np.inf, 0.0, 1e38, 3e38, 2.0 ** -126])
+@pytest.mark.parametrize("t", [None, np.inf, -np.inf, np.nan, 3e38])
+def test_targets_beyond_numbers_match_layer_by_layer(e, t):
+    """Infinite, zero and huge energies, infinite and undefined targets: finite
+    where the layer-by-layer step is, with the same infinities and NaN."""
+    x, img, e0 = data(64, 32, 20, 1)
+    img[3] = img[60] = 0.0 if e is None or e >= 1.0 else 1e-30
+    if e is not None:
+        e0[3] = e0[60] = float(e)
+    if t is not None:
+        img[5, 7] = img[61, 19] = float(t)
+    a, b = S.MLP([32, 256, 256, 40], seed=1), S.MLP([32, 256, 256, 40], seed=1)
+    assert a._train_bytes(x, img) > 0
+    la = a.train_step(x, img, e0, s_clamp=5.0, mse_mean=True, y_scale=1.0)
+    lb = layer_by_layer(b, x, img, e0, 1e-3, 5.0, True, 1.0)
+    pairs = [(la, lb)] + [(getattr(a, k)[l], getattr(b, k)[l]) for k in ("mW", "mb", "W", "b") for l in range(3)]
+    for p, q in pairs:
+        assert torch.equal(p.isnan(), q.isnan())
+        assert torch.equal(torch.where(p.isinf(), p, 0.0), torch.where(q.isinf(), q, 0.0))
+        ok = q.isfinite()
+        assert not bool(ok.any()) or rel(p[ok], q[ok]) < 1e-3
