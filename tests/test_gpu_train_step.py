@@ -138,3 +138,47 @@ def test_targets_beyond_numbers_match_layer_by_layer(e, t):
         assert torch.equal(torch.where(p.isinf(), p, 0.0), torch.where(q.isinf(), q, 0.0))
         ok = q.isfinite()
         assert not bool(ok.any()) or rel(p[ok], q[ok]) < 1e-3
+
+
+@pytest.mark.parametrize("B,dims", [
+    (192, [32, 256, 256, 40]),                                # the first fold of partial sums, and around it
+    (200, [32, 256, 256, 40]),
+    (256, [256, 256, 256, 128]),
+    (1032, [32, 256, 256, 256, 256, 1288]),
+    (8192, [32, 256, 256, 256, 256, 40]),                     # the per-layer head
+    (8192, [32, 256, 256, 256, 256, 10240]),                  # the image model
+])
+def test_gradients_no_further_from_float64_than_layer_by_layer(B, dims):
+    """Weight and bias gradients (with b1 = 0 a step's first moments) against
+    float64 products of the same bf16 values.  Weights: the root mean square
+    error is no larger than that of the layer-by-layer products (the same sums
+    up to 256 rows, then at most 320 rows in one accumulator where theirs has
+    256 to 1,184).  Biases: at most 2 B / 192 + 12 roundings to 24 bits in a
+    row (rows of a thread, 32 threads in pairs, parts)."""
+    print(f"gradients: batch {B}, layers {dims}", flush=True)
+    D, ys = dims[-1] // 2, 20.0
+    x, img, e0 = data(B, dims[0], D, B)
+    a, b = S.MLP(dims, seed=3), S.MLP(dims, seed=3)
+    a._train_fused(x, img, e0, 1e-3, 20.0, False, ys, a._train_bytes(x, img), b1=0.0)
+    out, acts, pres = b.forward(x, keep=True)
+    dout = torch.empty(out.shape, dtype=torch.int16, device="cuda")
+    loss = torch.zeros(1, device="cuda")
+    S._check(S._lib().supa_nll_grad(S._stream(), B, D, S._p(out), S._p(img), S._p(e0), ys, 20.0, 0, S._p(dout),
+                                    S._p(loss)))
+    dWs, dbs = b.backward(acts, pres, dout)
+    g = dout
+    grads = [None] * len(dWs)
+    for l in range(len(dWs) - 1, -1, -1):                     # (the values that b.backward went through)
+        grads[l] = g
+        if l > 0:
+            gn = torch.empty((B, dims[l]), dtype=torch.int16, device="cuda")
+            S.gemm(g, b.Wb[l], gn, trans_a=0, trans_b=1, epilogue=3, pre=pres[l - 1])
+            g = gn
+    rms = lambda m, ref: float((m.double() - ref).square().mean().sqrt())
+    for l in range(len(dWs)):
+        h, g = (S.bf16_to_float(t[l]).double() for t in (acts, grads))
+        for name, one, two, ref in (("W", a.mW[l], dWs[l], h.t().contiguous() @ g), ("b", a.mb[l], dbs[l], g.sum(0))):
+            err = [rms(t, ref) / rms(ref, 0.0) for t in (one, two)]
+            print(f"  layer {l} {name}: {err[0]:.3g}, layer by layer {err[1]:.3g}", flush=True)
+        assert rms(a.mW[l], h.t().contiguous() @ g) <= rms(dWs[l], h.t().contiguous() @ g), l
+        assert bool(((a.mb[l].double() - g.sum(0)).abs() <= (B / 96 + 12) * 2.0 ** -24 * g.abs().sum(0)).all()), l
