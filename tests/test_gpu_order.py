@@ -118,3 +118,41 @@ def test_pipelined_calls_some_of_them_empty(sizes):
             assert torch.equal(o["counts"], ref["counts"]) and torch.equal(o["ledger"], ref["ledger"])
             assert all(o[k] == ref[k] for k in ("total_hits", "total_nodes", "total_steps"))
             assert m > 0 or o["total_steps"] == 0
+
+
+def by_key(o, pre, col, fields):
+    """A call's records in the order of showers and path ids (segments follow one another)."""
+    c = o["counts"][:, col].long()
+    shower = torch.repeat_interleave(torch.arange(c.numel(), device=c.device), c)
+    m = shower.numel()
+    i = o[pre + "_key"][:m].argsort()
+    i = i[shower[i].argsort(stable=True)]
+    return [o[f"{pre}_{f}"][:m][i] for f in fields]
+
+
+# subtree items, orders of both kinds and no order in one entry, either way round
+@pytest.mark.parametrize("sizes", [[200, 40000, 4097, 3000, 33000, 100], [4097, 200, 5000, 40000, 3000]])
+def test_pipelined_calls_of_every_kind_share_one_layout(sizes):
+    print(f"order: calls of {sizes} showers in one, every output", flush=True)
+    w = workloads.WORKLOADS["e10_normal_5planes_1k"]
+    geom = workloads.geometry(w, n_planes=12, img_nx=8, img_ny=8, img_x0=-4.0, img_x1=4.0,
+                              img_y0=-4.0, img_y1=4.0)
+    data = ics(sum(sizes), "wide")
+    sim = supa.Simulator(geom, supa.OUT_HITS | supa.OUT_KEYS | supa.OUT_TREE | supa.OUT_IMAGES)
+    calls = [(sum(sizes[:j]), m) for j, m in enumerate(sizes)]
+    alone = [sim.simulate(*[t[s0:s0 + m].contiguous() for t in data], 7, shower_id_base=s0) for s0, m in calls]
+    outs = [sim.allocate(m, r["total_hits"], r["total_nodes"]) for (_, m), r in zip(calls, alone)]
+    for _ in range(2):
+        for o in outs:
+            o["images"].fill_(-1.0)
+            o["hit_key"].zero_()
+            o["node_key"].zero_()
+        assert sim.run_batches(*data, 7, calls, outs) == 0
+        for o, r in zip(outs, alone):
+            for k in ("counts", "ledger", "hit_offsets", "node_offsets", "images"):
+                assert torch.equal(o[k], r[k]), k
+            for a, b in zip(by_key(o, "hit", 1, ("x", "y", "e", "layer", "key")) +
+                            by_key(o, "node", 0, ("gen", "vx", "vy", "vz", "e", "key")),
+                            by_key(r, "hit", 1, ("x", "y", "e", "layer", "key")) +
+                            by_key(r, "node", 0, ("gen", "vx", "vy", "vz", "e", "key"))):
+                assert torch.equal(a, b)
