@@ -314,9 +314,12 @@ supa_status supa_set_launch(supa_ctx *ctx, int32_t waves_per_cu, int32_t frontie
  *                Counts-only calls use one.
  *   cost_order   1: showers are handed to the propagation kernel most
  *                expensive first (expected cost grows with E0; a device
- *                counting sort on log2 of the fixed-point energy), so the
- *                end of a launch is filled with cheap showers; 0: batch
- *                order; -1 (default): automatic.
+ *                counting sort on the fixed-point energy's exponent and five
+ *                leading mantissa bits), so the end of a launch is filled
+ *                with cheap showers; 0: batch order; -1 (default): automatic
+ *                -- when the call has more showers than waves, one sub-batch
+ *                and more than 8 planes, and from 65,536 showers otherwise
+ *                (supa_simulate_noalloc: always from 65,536).
  */
 supa_status supa_set_schedule(supa_ctx *ctx, int32_t sub_batches, int32_t cost_order);
 

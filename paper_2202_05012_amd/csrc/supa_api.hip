@@ -76,7 +76,9 @@ static constexpr int kItemCap = 16384, kShareCap = 16384;
 // E0 <= 100 stays below it, where sharing costs more than it gives
 static constexpr int kExpand = 256;
 static constexpr int kFixedItemCap = 1024, kFixedShareCap = 1024;
-static constexpr int64_t kAutoOrderMin = 65536;     // automatic cost order: from this batch size
+// Automatic work order: from this batch size in any case (sub-batches, the fixed
+// array, few planes), else from the first shower that has to wait (prepare).
+static constexpr int64_t kAutoOrderMin = 65536;
 
 // Scratch of supa_simulate_noalloc: one fixed array per GPU, held from the
 // library's first use of a device until the process ends.  Host code never
