@@ -574,8 +574,8 @@ __global__ void __launch_bounds__(512) train_backward_kernel(TrainArgs a) {
 // to some thousand rows, too many for one float accumulator: every three steps
 // (192 rows) the sums move to a second set of registers.  Root mean square
 // error against float64, 8,192 rows, 10,240 outputs: 4.9e-8 (2,752 rows in one
-// accumulator 1.6e-7; the layer-by-layer products, 1,184 rows, 8.2e-8), the
-// whole step 346 us with and without.
+// accumulator 1.6e-7; the layer-by-layer products, 1,184 rows, 8.2e-8), in
+// 70.0 us against 69.5.
 // ---------------------------------------------------------------------------
 constexpr int WG_N = 128, WG_K = 64;
 
@@ -638,40 +638,67 @@ __device__ __forceinline__ void wg_clear(WgSums &S) {
     for (int q = 0; q < 8; ++q) S.b[q] = 0.0f;
 }
 
-__device__ __forceinline__ void wg_add(WgSums &T, const WgSums &S) {
+// adds S to T and clears it
+__device__ __forceinline__ void wg_fold(WgSums &T, WgSums &S) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) T.w[i][j] += S.w[i][j];
 #pragma unroll
     for (int q = 0; q < 8; ++q) T.b[q] += S.b[q];
+    wg_clear(S);
 }
 
-__device__ __forceinline__ void wg_step(WgTile &T, WgSums &S, int wk, int wn, int lane) {
+// the operands of 16 rows
+struct WgOps {
+    u32x4_t x[2], y[2];
+};
+
+__device__ __forceinline__ void wg_read(WgTile &T, WgOps &O, int kk, int wk, int wn, int lane) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        u32x4_t x[2], y[2];
+    for (int i = 0; i < 2; ++i) O.x[i] = wg_operand<512>(&T.a[0], wk + 32 * i, kk, lane);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) x[i] = wg_operand<512>(&T.a[0], wk + 32 * i, kk, lane);
+    for (int j = 0; j < 2; ++j) O.y[j] = wg_operand<256>(&T.g[0], wn + 32 * j, kk, lane);
+}
+
+__device__ __forceinline__ void wg_mul(WgSums &S, const WgOps &O) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) y[j] = wg_operand<256>(&T.g[0], wn + 32 * j, kk, lane);
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) S.w[i][j] = mfma32(x[i], y[j], S.w[i][j]);
-    }
+        for (int j = 0; j < 2; ++j) S.w[i][j] = mfma32(O.x[i], O.y[j], S.w[i][j]);
+}
+
+// A step's products and bias sums; `meanwhile` runs while its first operands are
+// on their way (left to itself the compiler issues the copies of a later step
+// first, and reads no operand ahead: 74 us instead of 70 for the kernel).
+template <typename F>
+__device__ __forceinline__ void wg_step(WgTile &T, WgSums &S, int wk, int wn, int lane, F &&meanwhile) {
+    WgOps p, q;
+    wg_read(T, p, 0, wk, wn, lane);
+    wg_read(T, q, 1, wk, wn, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    meanwhile();
+    wg_mul(S, p);
+    wg_read(T, p, 2, wk, wn, lane);
+    wg_mul(S, q);
+    wg_read(T, q, 3, wk, wn, lane);
     // bias: this thread's chunk (of 16) of two rows
+    u32x4_t v[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int m = ((int)threadIdx.x >> 4) + 32 * r;
         const int at = 256 * m + 16 * (((int)threadIdx.x & 15) ^ tr_swizzle(m));
-        const u32x4_t v = *(const u32x4_t *)(&T.g[0] + at);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            S.b[2 * q] += bf_to_f(v[q] & 0xffffu);
-            S.b[2 * q + 1] += bf_to_f(v[q] >> 16);
-        }
+        v[r] = *(const u32x4_t *)(&T.g[0] + at);
     }
+    wg_mul(S, p);
+    wg_mul(S, q);
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            S.b[2 * t] += bf_to_f(v[r][t] & 0xffffu);
+            S.b[2 * t + 1] += bf_to_f(v[r][t] >> 16);
+        }
 }
 
 __global__ void __launch_bounds__(512) train_weight_grad_kernel(TrainArgs a) {
@@ -699,25 +726,26 @@ __global__ void __launch_bounds__(512) train_weight_grad_kernel(TrainArgs a) {
     wg_clear(sum);
     wg_clear(acc);
     // (see train_input_grad_kernel; six copy instructions per wave and step)
-#define WG_STAGE(S, CUR, FREE)                                                            \
-    meet<6>();                                                                            \
-    wg_issue(J, a.B, m_begin + WG_K * min((S) + 2, steps - 1), FREE, wave, lane);         \
-    wg_step(CUR, acc, wk, wn, lane);
-    wg_issue(J, a.B, m_begin, T0, wave, lane);
-    wg_issue(J, a.B, m_begin + WG_K * min(1, steps - 1), T1, wave, lane);
+    auto none = [] {};
+    auto issue = [&](int step, WgTile &T) { wg_issue(J, a.B, m_begin + WG_K * min(step, steps - 1), T, wave, lane); };
+    issue(0, T0);
+    issue(1, T1);
     int s = 0;
     for (; s + 3 <= steps; s += 3) {
-        wg_add(sum, acc);
-        wg_clear(acc);
-        WG_STAGE(s, T0, T2)
-        WG_STAGE(s + 1, T1, T0)
-        WG_STAGE(s + 2, T2, T1)
+        meet<6>();
+        wg_step(T0, acc, wk, wn, lane, [&] {
+            issue(s + 2, T2);
+            wg_fold(sum, acc);
+        });
+        meet<6>();
+        wg_step(T1, acc, wk, wn, lane, [&] { issue(s + 3, T0); });
+        meet<6>();
+        wg_step(T2, acc, wk, wn, lane, [&] { issue(s + 4, T1); });
     }
     meet<0>();
-    if (s < steps) wg_step(T0, acc, wk, wn, lane);
-    if (s + 1 < steps) wg_step(T1, acc, wk, wn, lane);
-    wg_add(sum, acc);
-#undef WG_STAGE
+    if (s < steps) wg_step(T0, acc, wk, wn, lane, none);
+    if (s + 1 < steps) wg_step(T1, acc, wk, wn, lane, none);
+    wg_fold(sum, acc);
     float *out = a.dw + a.dw_off[l] + (int64_t)part * J.in * J.out;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
